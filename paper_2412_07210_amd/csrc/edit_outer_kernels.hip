@@ -193,6 +193,77 @@ __device__ __forceinline__ double wave_sum(double x) {
   return x;
 }
 
+// Two doubles a, b exchanged between the halves of every 2B lanes (B = 32 or
+// 16): x takes the lower halves of a and of b, y the upper halves.
+template <int B>
+__device__ __forceinline__ void swap_halves(double a, double b, double& x, double& y) {
+  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+  const unsigned alo = __double2loint(a), ahi = __double2hiint(a);
+  const unsigned blo = __double2loint(b), bhi = __double2hiint(b);
+  u32x2 lo, hi;
+  if constexpr (B == 32) {
+    lo = __builtin_amdgcn_permlane32_swap(alo, blo, false, false);
+    hi = __builtin_amdgcn_permlane32_swap(ahi, bhi, false, false);
+  } else {
+    lo = __builtin_amdgcn_permlane16_swap(alo, blo, false, false);
+    hi = __builtin_amdgcn_permlane16_swap(ahi, bhi, false, false);
+  }
+  x = __hiloint2double(hi[0], lo[0]);
+  y = __hiloint2double(hi[1], lo[1]);
+}
+
+// A double from another lane of the 16-lane row (DPP control CTRL).
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double a) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(a), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(a), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+
+// The sums over a wave's 64 lanes of M values at once (M <= 64): each step
+// adds two lanes' values and leaves half of the values in either half of the
+// lanes, so that after six steps every lane holds one finished sum, the one
+// that index(lane) names (a sum that several lanes name has the same bits in
+// all of them).  36 values take about 150 vector instructions and no LDS
+// access, where a butterfly per value takes 432 LDS permutes per wave: at
+// K = 8 that closing reduction was most of the Gram pass's fixed cost (on
+// 2,048 bf16 elements the pass took 11.3 us with it and takes 4.8 us with
+// this one; 1,024 fp32 elements at K = 4: 5.0 and 3.0).  The order of the
+// additions is fixed, so results are reproducible.
+template <int B, int M>
+struct WaveSums {
+  static_assert(M >= 1 && M <= 64, "one sum per lane at most");
+  static constexpr int H = (M + 1) / 2;
+  static __device__ __forceinline__ double sum(const double (&x)[M], int lane) {
+    double y[H];
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      const double p = x[2 * i], q = x[2 * i + 1 < M ? 2 * i + 1 : 2 * i];  // an odd last value pairs with itself
+      if constexpr (B >= 16) {
+        double a, b;
+        swap_halves<B>(p, q, a, b);
+        y[i] = a + b;
+      } else {
+        // partner lanes: rotate by 8, mirror of 8, the quad's xor 2 and xor 1
+        constexpr int kCtrl = B == 8 ? 0x128 : B == 4 ? 0x141 : B == 2 ? 0x4E : 0xB1;
+        const bool up = (lane & B) != 0;
+        const double send = up ? p : q, keep = up ? q : p;
+        y[i] = keep + dpp_move<kCtrl>(send);
+      }
+    }
+    if constexpr (B > 1)
+      return WaveSums<B / 2, H>::sum(y, lane);
+    else
+      return y[0];
+  }
+  static __device__ __forceinline__ int index(int lane) {
+    int i = 0;
+    if constexpr (B > 1) i = WaveSums<B / 2, H>::index(lane);
+    i = 2 * i + ((lane & B) ? 1 : 0);
+    return i < M - 1 ? i : M - 1;
+  }
+};
+
 __device__ __forceinline__ int pair_index(int K, int j, int k) {  // j <= k
   return j * K - (j * (j - 1)) / 2 + (k - j);
 }
@@ -925,14 +996,13 @@ __global__ __launch_bounds__(kFusedThreads) void fused_mean_kernel(float* __rest
     for (int j = 0; j < K; ++j) store_scalar<BF16>(reps.p[j], tail, tn);
   }
 
-  // block sums in a fixed order: wave butterfly, then the waves in order
+  // block sums in a fixed order: the wave's, then the waves in order
   constexpr int kWaves = kFusedThreads / 64;
   __shared__ double red[kWaves][K + 1];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int p = 0; p <= K; ++p) {
-    const double t = wave_sum(sq[p]);
-    if (lane == 0) red[wave][p] = t;
+  {
+    const int lane = threadIdx.x & 63;
+    const double t = WaveSums<32, K + 1>::sum(sq, lane);
+    red[threadIdx.x >> 6][WaveSums<32, K + 1>::index(lane)] = t;
   }
   __syncthreads();
   if (threadIdx.x <= K) {  // the block's K + 1 sums, contiguous
