@@ -163,15 +163,14 @@ edit_status_t edit_outer_step_layer(edit_outer_t h, int32_t layer, float *theta,
 /* One outer round: `count` distinct units, stepped in the given (forward)
  * order on `stream` (the layer-wise synchronization of Sec. 3.1), with the
  * same results bit for bit as calling edit_outer_step_layer for each of them
- * in that order.  Up to K = 8 each unit's one-block decision runs inside
- * the next pass-1 launch (an extra block), and its update pass follows that
- * launch; two consecutive units (not the round's last) share one pass-1
- * launch, whose partial sums are those of their own launches.  Above K = 8
- * a unit's update pass follows its own pass 1 and decision.  A unit of at
- * most 256 16-byte vectors (2,048 bf16 or 1,024 fp32 elements) is stepped
- * whole by one block of a small launch that carries up to four such units.
- * Units that kernel timing (edit_outer_set_profiling) covers keep launches
- * of their own.
+ * in that order.  Consecutive units are stepped in batches of up to 16 (8
+ * above K = 16), each batch with one Gram launch, one launch of its units'
+ * one-block decisions and one update launch; the partial sums of a unit do
+ * not depend on its batch.  A unit of at most 256 16-byte vectors (2,048
+ * bf16 or 1,024 fp32 elements) is stepped whole by one block of a small
+ * launch that carries up to as many such units, after the batches before
+ * it.  Units that kernel timing (edit_outer_set_profiling) covers keep
+ * launches of their own.
  *   layers   [count] unit indices, each at most once (else EDIT_EINVAL)
  *   theta    [count] device pointers, as in edit_outer_step_layer
  *   momentum [count] device pointers
@@ -277,14 +276,14 @@ const char *edit_outer_last_error(void);
  * Arguments, ownership and errors as in edit_outer_step_layer, plus
  * EDIT_EINVAL when the handle was made with EDIT_ONE_PASS, or when the
  * unit's partials exceed the array: K(K+1)/2 doubles per Gram-pass block,
- * whose count grows with the unit up to one block per CU above K = 8 (255
- * on MI355X), so only K = 32 units of more than 63,488 16-byte vectors
+ * whose count grows with the unit up to one block per CU (256 on MI355X),
+ * so only K = 32 units of more than 63,488 16-byte vectors
  * (507,904 bf16 or 253,952 fp32 elements) are refused there.
  * All calls on one GPU share that GPU's array, which keeps the last call's
  * partials (nothing in it needs clearing: a call writes every partial it
  * reads).  Calls on one GPU must therefore not overlap: order them on one
  * stream or with events, also across handles and host threads; overlapping
- * calls race.  The call enqueues three kernels and one event record and
+ * calls race.  The call enqueues up to three kernels and one event record and
  * makes no synchronising call, so it can be captured into a HIP graph and
  * replayed; after a replay, once the caller has synchronised,
  * edit_outer_state_get reports that replay's step. */
@@ -360,9 +359,7 @@ void edit_group_destroy(edit_group_t h);
 edit_status_t edit_outer_set_profiling(edit_outer_t h, int32_t every);
 
 /* Durations in ms of the last profiled step of `layer`: ms[0] its norm/Gram
- * pass plus its decision kernel (in a round: its own norm/Gram launch, which
- * up to K = 8 also carries the decisions of the one or two units before it),
- * ms[1] its update pass.  With EDIT_ONE_PASS: ms[0] the fused pass, ms[1]
+ * pass plus its decision kernel, ms[1] its update pass.  With EDIT_ONE_PASS: ms[0] the fused pass, ms[1]
  * the record reduction when the unit was stepped alone (0 in a round, which
  * reduces all units in one launch at its end).  Waits for it. */
 edit_status_t edit_outer_kernel_times(edit_outer_t h, int32_t layer, float ms[2]);

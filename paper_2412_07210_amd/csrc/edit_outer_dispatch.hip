@@ -16,33 +16,25 @@ const KernelSet* kernels_for(int K) {
 
 }  // namespace
 
-hipError_t launch_pass1(int K, bool bf16, int rows, const float* theta, const void* const* reps,
-                        int64_t n, double* partials, const double* prev_partials, int prev_rows,
-                        UnitRecord* prev_rec, const DecideParams& prm, hipStream_t stream) {
+hipError_t launch_gram(int K, bool bf16, const UnitDesc* unit, int count, int max_blocks, hipStream_t stream) {
   const KernelSet* s = kernels_for(K);
-  return s ? s->pass1(bf16, rows, theta, reps, n, partials, prev_partials, prev_rows, prev_rec, prm, stream)
-           : hipErrorInvalidValue;
+  return s ? s->gram(bf16, unit, count, max_blocks, stream) : hipErrorInvalidValue;
 }
 
-hipError_t launch_pass1_pair(int K, bool bf16, const Pass1Desc* unit, int count, const DecideDesc* prev,
-                             int nprev, const DecideParams& prm, hipStream_t stream) {
-  if (count < 1 || count > 2 || nprev < 0 || nprev > 2) return hipErrorInvalidValue;
+hipError_t launch_decide(int K, const UnitDesc* unit, int count, const DecideParams& prm, hipStream_t stream) {
   const KernelSet* s = kernels_for(K);
-  return s ? s->pass1_pair(bf16, unit, count, prev, nprev, prm, stream) : hipErrorInvalidValue;
+  return s ? s->decide(unit, count, prm, stream) : hipErrorInvalidValue;
 }
 
-hipError_t launch_round_small(int K, bool bf16, const DecideDesc* prev, int nprev, const DecideParams& prm,
-                              const SingleBlockDesc* unit, int count, double lr, double rho,
-                              hipStream_t stream) {
-  if (count < 0 || count > kMaxSingleBlockUnits || nprev < 0 || nprev > 2) return hipErrorInvalidValue;
+hipError_t launch_small_step(int K, bool bf16, const UnitDesc* unit, int count, const DecideParams& prm, double lr,
+                             double rho, hipStream_t stream) {
   const KernelSet* s = kernels_for(K);
-  return s ? s->round_small(bf16, prev, nprev, prm, unit, count, lr, rho, stream) : hipErrorInvalidValue;
+  return s ? s->small_step(bf16, unit, count, prm, lr, rho, stream) : hipErrorInvalidValue;
 }
 
-hipError_t launch_decide(int K, const double* partials, int rows, UnitRecord* rec, const DecideParams& prm,
-                         hipStream_t stream) {
+int batch_units(int K) {
   const KernelSet* s = kernels_for(K);
-  return s ? s->decide(partials, rows, rec, prm, stream) : hipErrorInvalidValue;
+  return s ? s->batch_units : 1;
 }
 
 hipError_t launch_gram_reduce(int K, const double* partials, int rows, double* gram, hipStream_t stream) {
@@ -56,10 +48,10 @@ hipError_t launch_decide_gram(int K, const double* gram, UnitRecord* rec, const 
   return s ? s->decide_gram(gram, rec, prm, stream) : hipErrorInvalidValue;
 }
 
-hipError_t launch_pass2(int K, bool bf16, int blocks, int lds, float* theta, float* mom, void* const* reps,
-                        const UnitRecord* rec, int64_t n, double lr, double rho, hipStream_t stream) {
+hipError_t launch_update(int K, bool bf16, const UnitDesc* unit, int count, int lds, double lr, double rho,
+                         hipStream_t stream) {
   const KernelSet* s = kernels_for(K);
-  return s ? s->pass2(bf16, blocks, lds, theta, mom, reps, rec, n, lr, rho, stream) : hipErrorInvalidValue;
+  return s ? s->update(bf16, unit, count, lds, lr, rho, stream) : hipErrorInvalidValue;
 }
 
 // The update pass streams 2K + 4 buffers at once (K + 2 read, K + 2
@@ -116,11 +108,6 @@ hipError_t launch_pattern_probe(int K, bool bf16, int blocks, int lds, float* th
                                 int64_t n, hipStream_t stream) {
   const KernelSet* s = kernels_for(K);
   return s ? s->pattern_probe(bf16, blocks, lds, theta, mom, reps, n, stream) : hipErrorInvalidValue;
-}
-
-int pass1_blocks_per_cu(int K, bool bf16) {
-  const KernelSet* s = kernels_for(K);
-  return s ? s->pass1_blocks_per_cu(bf16) : 1;
 }
 
 }  // namespace edit

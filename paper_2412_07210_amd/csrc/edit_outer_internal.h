@@ -9,8 +9,9 @@
 
 namespace edit {
 
-constexpr int kThreads = 256;        // threads per block of the Gram pass
-constexpr int kPass2Threads = 64;    // threads per block of the update pass (one wave)
+constexpr int kRowVectors = 256;     // 16-byte vectors per Gram partial row, at least (up to one row per CU)
+constexpr int kUpdateThreads = 64;   // threads per block of the update pass (one wave)
+constexpr int kCopyThreads = 256;     // threads per block of the copy probe
 constexpr int kFusedThreads = 64;    // threads per block of the one-pass mean step (one wave)
 constexpr int kMaxK = EDIT_MAX_K;
 constexpr int kMaxPairs = kMaxK * (kMaxK + 1) / 2;
@@ -49,32 +50,25 @@ struct DecideParams {
   uint32_t flags;
 };
 
-// A unit of a round whose Gram pass is a single block, stepped whole (Gram
-// row, decision, update) by one block of a small launch.
-constexpr int kMaxSingleBlockUnits = 4;  // per launch
-struct SingleBlockDesc {
+// One unit of a launch; a launch takes a batch of them.
+constexpr int kMaxBatchUnits = 16;  // half of it above K = 16
+struct UnitDesc {
   float* theta;
   float* mom;
-  void* const* reps;  // host array of K device pointers (read at launch)
-  double* partials;
-  UnitRecord* rec;
+  void* const* reps;   // host array of K device pointers (read at launch)
   int64_t n;
+  int64_t cut;         // Gram pass up to K = 8: first element read through the cache
+  double* partials;    // [rows][K(K+1)/2]
+  UnitRecord* rec;
+  int32_t rows;        // blocks (= partial rows) of the Gram pass
+  int32_t update_blocks;
 };
 
-// A unit whose decision block 0 of a launch takes (see launch_pass1_pair).
+// A unit whose decision one block takes.
 struct DecideDesc {
   const double* partials;
-  int rows;
   UnitRecord* rec;
-};
-
-// One unit of a two-unit Gram launch.
-struct Pass1Desc {
-  const float* theta;
-  const void* const* reps;  // host array of K device pointers (read at launch)
-  int64_t n;
-  double* partials;
-  int rows;
+  int32_t rows;
 };
 
 // The kernels specialised for one K, behind plain function pointers.  The
@@ -87,25 +81,20 @@ struct Pass1Desc {
 #define EDIT_KERNEL_SET_FN(first) EDIT_KERNEL_SET_FN2(first)
 
 struct KernelSet {
-  hipError_t (*pass1)(bool bf16, int rows, const float* theta, const void* const* reps, int64_t n,
-                      double* partials, const double* prev_partials, int prev_rows, UnitRecord* prev_rec,
-                      const DecideParams& prm, hipStream_t stream);
-  hipError_t (*pass1_pair)(bool bf16, const Pass1Desc* unit, int count, const DecideDesc* prev, int nprev,
-                           const DecideParams& prm, hipStream_t stream);
-  hipError_t (*round_small)(bool bf16, const DecideDesc* prev, int nprev, const DecideParams& prm,
-                            const SingleBlockDesc* unit, int count, double lr, double rho, hipStream_t stream);
-  hipError_t (*decide)(const double* partials, int rows, UnitRecord* rec, const DecideParams& prm,
-                       hipStream_t stream);
+  hipError_t (*gram)(bool bf16, const UnitDesc* unit, int count, int max_blocks, hipStream_t stream);
+  hipError_t (*decide)(const UnitDesc* unit, int count, const DecideParams& prm, hipStream_t stream);
+  hipError_t (*small_step)(bool bf16, const UnitDesc* unit, int count, const DecideParams& prm, double lr,
+                           double rho, hipStream_t stream);
   hipError_t (*gram_reduce)(const double* partials, int rows, double* gram, hipStream_t stream);
   hipError_t (*decide_gram)(const double* gram, UnitRecord* rec, const DecideParams& prm, hipStream_t stream);
-  hipError_t (*pass2)(bool bf16, int blocks, int lds, float* theta, float* mom, void* const* reps,
-                      const UnitRecord* rec, int64_t n, double lr, double rho, hipStream_t stream);
+  hipError_t (*update)(bool bf16, const UnitDesc* unit, int count, int lds, double lr, double rho,
+                       hipStream_t stream);
   hipError_t (*fused_mean)(bool bf16, int rows, int lds, float* theta, float* mom, void* const* reps,
                            double* partials, UnitRecord* rec, int64_t n, double lr, double rho, hipStream_t stream);
   hipError_t (*fused_finish)(const FinishEntry* table, int units, hipStream_t stream);
-  int (*pass1_blocks_per_cu)(bool bf16);
   hipError_t (*pattern_probe)(bool bf16, int blocks, int lds, float* theta, float* mom, void* const* reps,
                               int64_t n, hipStream_t stream);
+  int batch_units;
   int fused_vectors_bf16, fused_vectors_f32;
 };
 
@@ -116,25 +105,15 @@ EDIT_K_RANGES(EDIT_DECLARE_SET)
 // Launchers (edit_outer_dispatch.hip, through the kernel sets).  All enqueue
 // on `stream` and return the launch status (hipErrorInvalidValue for a K
 // outside 1..EDIT_MAX_K); none synchronises.
-// Pass 1 over `rows` partial rows; when prev_partials is not null, one more
-// block takes the decision of the previous unit of a round (prev_rows rows,
-// record prev_rec) inside the same launch.
-hipError_t launch_pass1(int K, bool bf16, int rows, const float* theta,
-                        const void* const* reps, int64_t n, double* partials,
-                        const double* prev_partials, int prev_rows, UnitRecord* prev_rec,
-                        const DecideParams& prm, hipStream_t stream);
-// Pass 1 of `count` (1 or 2) units of a round in one launch, K <= 8 only:
-// each block writes its row of every unit (the rows of its own launch), and
-// block 0 takes the decisions of `nprev` (0 to 2) earlier units first.
-hipError_t launch_pass1_pair(int K, bool bf16, const Pass1Desc* unit, int count, const DecideDesc* prev,
-                             int nprev, const DecideParams& prm, hipStream_t stream);
-// A small launch of a round: the decisions of `nprev` (0 to 2) earlier
-// units and `count` whole single-block units.
-hipError_t launch_round_small(int K, bool bf16, const DecideDesc* prev, int nprev, const DecideParams& prm,
-                              const SingleBlockDesc* unit, int count, double lr, double rho,
-                              hipStream_t stream);
-hipError_t launch_decide(int K, const double* partials, int rows, UnitRecord* rec,
-                         const DecideParams& prm, hipStream_t stream);
+// Each takes a batch of 1 to batch_units(K) units.  The Gram pass: one
+// partial row per item, `max_blocks` (one per CU) persistent blocks.
+hipError_t launch_gram(int K, bool bf16, const UnitDesc* unit, int count, int max_blocks, hipStream_t stream);
+// The decisions from the partial rows.
+hipError_t launch_decide(int K, const UnitDesc* unit, int count, const DecideParams& prm, hipStream_t stream);
+// Whole steps of units of one partial row, a block each.
+hipError_t launch_small_step(int K, bool bf16, const UnitDesc* unit, int count, const DecideParams& prm, double lr,
+                             double rho, hipStream_t stream);
+int batch_units(int K);
 // The fixed-order sum of the partials as a K(K+1)/2 vector in device memory.
 hipError_t launch_gram_reduce(int K, const double* partials, int rows, double* gram,
                               hipStream_t stream);
@@ -143,9 +122,8 @@ hipError_t launch_decide_gram(int K, const double* gram, UnitRecord* rec, const 
                               hipStream_t stream);
 // The update pass; `lds` bytes of dynamic LDS per block (used by nothing)
 // cap its resident blocks per CU (update_pass_lds).
-hipError_t launch_pass2(int K, bool bf16, int blocks, int lds, float* theta, float* mom,
-                        void* const* reps, const UnitRecord* rec, int64_t n, double lr,
-                        double rho, hipStream_t stream);
+hipError_t launch_update(int K, bool bf16, const UnitDesc* unit, int count, int lds, double lr, double rho,
+                         hipStream_t stream);
 // Update-pass blocks resident per CU, and the dynamic LDS per block that
 // caps them there given the CU's LDS bytes.
 int update_pass_blocks_per_cu(int K);
@@ -164,12 +142,9 @@ hipError_t launch_fused_mean(int K, bool bf16, int rows, int lds, float* theta, 
 hipError_t launch_fused_finish(int K, const FinishEntry* table, int units, hipStream_t stream);
 hipError_t launch_copy(void* dst, const void* src, int64_t nbytes, int blocks,
                        hipStream_t stream);
-// Pass 2's loads and stores (whole vectors only) with no arithmetic.
+// The update pass's loads and stores (whole vectors only) with no arithmetic.
 hipError_t launch_pattern_probe(int K, bool bf16, int blocks, int lds, float* theta, float* mom, void* const* reps,
                                 int64_t n, hipStream_t stream);
-
-// Resident blocks per CU of the pass-1 kernel (for its persistent grid).
-int pass1_blocks_per_cu(int K, bool bf16);
 
 inline int num_pairs(int K) { return K * (K + 1) / 2; }
 

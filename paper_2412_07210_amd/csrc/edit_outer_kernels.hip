@@ -1,19 +1,20 @@
 // Device kernels of the EDiT outer synchronization step for gfx950.
 //
-// One step of one sync unit is three launches on one stream:
+// One step of a batch of sync units (one unit, or several small ones of a
+// round) is three launches on one stream:
 //
-//   pass1  streams theta and the K replicas once and accumulates, per block,
+//   gram   streams theta and the K replicas once and accumulates, per block,
 //          the upper triangle of the Gram matrix  Gram_jk = <Delta_j, Delta_k>
 //          of the pseudo gradients Delta_j = r_j - theta (Sec. 3.2).  The
 //          diagonal gives the module norms G_j; the off-diagonal terms give
 //          ||sum_j w_j Delta_j||^2 = w^T Gram w, so the clip factor of Eq. 4
 //          is known before the update pass and the step needs two streaming
 //          passes instead of three.
-//   decide one block: fixed-order reduction of the per-block partials, then
-//          one wave (worker j in lane j) takes the decision: EMA z-test and
-//          update (Eq. 1), rollback test, softmax weights (Eq. 2), Gbar and
-//          beta (Eq. 4), coefficients beta*w_j.
-//   pass2  streams theta, b and the replicas of the workers with a non-zero
+//   decide one block per unit: fixed-order reduction of the per-block
+//          partials, then one wave (worker j in lane j) takes the decision:
+//          EMA z-test and update (Eq. 1), rollback test, softmax weights
+//          (Eq. 2), Gbar and beta (Eq. 4), coefficients beta*w_j.
+//   update streams theta, b and the replicas of the workers with a non-zero
 //          coefficient, forms Delta_hat = sum_j beta w_j Delta_j (Eq. 3, 5),
 //          applies Nesterov momentum and writes theta, b and all K replicas.
 //
@@ -21,28 +22,30 @@
 // from the exact pseudo gradients on, rounded once when stored.
 //
 // The passes are HBM-bound (2-4 flop per byte at K = 8).  Lanes move 16-byte
-// vectors (global_load_dwordx4).  Pass 1 runs a persistent grid of one block
-// per CU holding all the waves the CU runs of it (grid-stride), so the chip
-// streams one contiguous window of every buffer at a time and the decision
-// reduces one partial row per CU; up to K = 8 each lane double-buffers its
-// vectors (the loads of trip t+1 are in flight while trip t is computed), so
-// the fp64 work hides under the memory latency even at 2 waves per SIMD.
-// Above K = 8 the Gram is a rank-n update on the fp64 matrix cores
+// vectors (global_load_dwordx4).  The Gram pass runs a persistent grid of one
+// block per CU (strided over the unit), so the chip streams one contiguous
+// window of every buffer at a time and the decision reduces one partial row
+// per CU; each lane double-buffers its vectors (the loads of trip t+1 are in
+// flight while trip t is computed), so the fp64 work hides under the memory
+// latency.  Above K = 8 the Gram is a rank-n update on the fp64 matrix cores
 // (v_mfma_f64_4x4x4f64 tiles), which the VALU could not hold in registers.
-// Pass 2, which writes as much as it reads, instead gives each thread one
-// vector and lets the block dispatcher order the traffic (see there).
+// The update pass, which writes as much as it reads, instead gives each
+// thread one vector and lets the block dispatcher order the traffic.
 //
-// Also here: the Gram pass of two units of a round in one launch
-// (pass1_gram_pair_kernel), the small launch of a round that steps units of
-// one Gram-pass block whole (round_small_kernel; the bodies of pass 1 and
-// pass 2 are the fragments gram_rows_valu.inc, gram_rows_mfma.inc and
-// update_vector_at.inc, shared with the kernels above), the Gram
-// export/import of a sharded module
+// The update pass follows its own Gram pass with only the decision between
+// them, so it finds the end of its input in the 256 MB Infinity Cache: the
+// Gram pass reads that end through the cache (everything before it
+// non-temporally) and the update pass takes its blocks from the end.
+//
+// Also here: the step of units of one Gram block in one block
+// (small_step_kernel; the bodies of the Gram and update passes are the
+// fragments gram_rows_valu.inc, gram_rows_mfma.inc and update_vector_at.inc,
+// shared with the kernels above), the Gram export/import of a sharded module
 // (gram_reduce_kernel, decide_gram_kernel), the one-pass mean step used when
 // no penalty component is on (fused_mean_kernel, fused_finish_kernel), and a
 // plain copy kernel for bandwidth and counter calibration.  Reductions go
-// wave shuffle -> LDS -> per-block partial -> one block in a fixed order, so
-// results are bitwise reproducible.
+// wave -> LDS -> per-block partial -> one block in a fixed order, so results
+// are bitwise reproducible.
 #include "edit_outer_internal.h"
 
 #include <algorithm>
@@ -60,6 +63,13 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float float2_t __attribute__((ext_vector_type(2)));
+
+// Cache policy of the streaming kernels: each pass touches every byte once;
+// non-temporal accesses measured ~15% faster for the VALU Gram pass and ~5%
+// for the update pass.  The matrix-core Gram pass, bound by issue, reads
+// through the cache.
+constexpr bool kNTMfma = false;
+constexpr bool kNT2 = true;
 
 template <int K>
 struct ConstPtrs {
@@ -172,18 +182,19 @@ __device__ __forceinline__ double delta64(const u32x4& raw, int e, float th) {
   return static_cast<double>(element<BF16>(raw, e)) - static_cast<double>(th);
 }
 
-// A field of a unit record read by the update pass.  When the record was
-// written earlier in the same launch (the single-block path, kFresh), the
-// load is a relaxed atomic at work-group scope: always a vector memory
-// instruction, which sees the other waves' stores once a barrier has
-// ordered them, whereas a scalar-cache load could return stale data.  A
-// record written by an earlier launch is read with a plain load.
-template <bool kFresh, typename T>
+// A field of a unit record read by the update pass: from LDS where the block
+// has just made the record (the single-block step), otherwise from a record
+// that an earlier launch wrote, constant for this one and read as such, by
+// scalar loads.  As plain loads beside stores that the compiler cannot tell
+// apart from it, the fields came by vector loads and every replica pointer
+// was chosen per lane (K = 16 update pass 750 us against 680 with scalar
+// loads, K = 8 415 against 409).
+template <bool kInLds, typename T>
 __device__ __forceinline__ T rec_load(const T* p) {
-  if constexpr (kFresh)
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-  else
+  if constexpr (kInLds)
     return *p;
+  else
+    return *reinterpret_cast<const __attribute__((address_space(4))) T*>(reinterpret_cast<uintptr_t>(p));
 }
 
 // Sum over the 64 lanes of a wave, fixed butterfly order (same in every lane).
@@ -271,35 +282,47 @@ __device__ __forceinline__ int pair_index(int K, int j, int k) {  // j <= k
 // ------------------------------------------------------------- decision
 
 constexpr int kDecideThreads = 1024;  // one block; wide so the partial loads overlap
-constexpr int kReduceLogical = 1024;  // logical threads of the partial reduction
 
-// Reduce the per-block Gram partials [NP][rows] in a fixed order into
-// gram[NP] (shared memory).  Logical thread lt takes pair lt / T and rows
-// lt % T, lt % T + T, ... (T phases per pair, at most 64), with 16 loads in
-// flight, and the T phase sums of a pair are then added in phase order.
-// The partials were just written by every XCD's blocks, so the loads come
-// from the Infinity Cache or HBM and the reduction is latency-bound: many
-// independent loads per thread matter more than anything else here.  The
-// order depends on neither the block size nor the unrolling, so a standalone
-// decision kernel, one folded into a pass-1 launch and the Gram export agree
-// bit for bit.  `scratch` holds kReduceLogical doubles of shared memory.
-template <int K, int kBlockThreads>
+// Reduce a unit's partial rows [rows][NP] in a fixed order into gram[NP]
+// (shared memory).  Thread t reads the flat array at t, t + S, t + 2S, ...
+// with S the largest multiple of NP within the block, so it always reads
+// column t % NP and a wave's loads are contiguous; the S threads' sums are
+// then added per column in thread order.  The rows were just written by
+// every XCD's blocks, so the loads come from the Infinity Cache or HBM and
+// the reduction is latency-bound: all of a thread's loads for 256 rows are
+// in flight at once up to K = 16, 48 at a time above.  As [NP][rows], whose
+// loads touched a cache line per lane, over up to 1,023 rows the decision
+// kernel took 9.2 us at K = 4 (1.05M fp32 elements; now 4.4), 6.8 at K = 8
+// (4.7) and 79 at K = 32 (27, bound by one CU reading 1.1 MB).
+template <int K>
 __device__ void reduce_partials(const double* partials, int rows, double* gram, double* scratch) {
   constexpr int NP = K * (K + 1) / 2;
-  constexpr int T = kReduceLogical / NP < 64 ? kReduceLogical / NP : 64;
-  for (int lt = threadIdx.x; lt < NP * T; lt += kBlockThreads) {
-    const int p = lt / T, ph = lt % T;
-    const double* src = partials + static_cast<int64_t>(p) * rows;
+  constexpr int T = kDecideThreads / NP;
+  constexpr int S = NP * T;
+  constexpr int kAll = (256 + T - 1) / T;
+  constexpr int U = kAll < 48 ? kAll : 48;
+  const int t = threadIdx.x;
+  if (t < S) {
+    const int total = rows * NP;
     double acc = 0.0;
-#pragma unroll 16
-    for (int r = ph; r < rows; r += T) acc += __builtin_nontemporal_load(src + r);
-    scratch[lt] = acc;
+    for (int i = t; i < total; i += S * U) {
+      double x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int at = i + u * S;
+        x[u] = at < total ? __builtin_nontemporal_load(partials + at) : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) acc += x[u];
+    }
+    scratch[t] = acc;
   }
   __syncthreads();
-  for (int p = threadIdx.x; p < NP; p += kBlockThreads) {
-    double g = 0.0;
-    for (int ph = 0; ph < T; ++ph) g += scratch[p * T + ph];
-    gram[p] = g;
+  if (t < NP) {
+    double g = scratch[t];
+#pragma unroll
+    for (int k = 1; k < T; ++k) g += scratch[k * NP + t];
+    gram[t] = g;
   }
 }
 
@@ -411,41 +434,21 @@ __device__ void decide(const double* gram, UnitRecord* rec, const DecideParams& 
   }
 }
 
-// ---------------------------------------------------------------- pass 1
-
-// The decision of the previous unit of a round, taken by block 0 of a pass-1
-// launch (partials == nullptr: none).  The previous unit's pass 1 finished
-// before this launch began, so its partials are visible, and its decision
-// costs no serial time of its own.
-struct PrevDecide {
-  const double* partials;
-  int rows;
-  UnitRecord* rec;
-};
+// ------------------------------------------------------------- Gram pass
 
 // Threads per block of the Gram pass.  The MFMA version runs one block per
 // CU holding all its resident waves (3 per SIMD up to K = 16, 2 above, where
 // the 21 to 36 accumulator tiles and the double-buffered vectors of eight
 // worker groups need up to 256 VGPRs per lane), so the block reduction
-// combines them and the decision reduces one partial row per CU: at K = 16
-// that row count (255 against 767) took the decision from 26 to 12 us.  The
-// VALU version keeps 256-thread blocks: one 512-thread block per CU shortened
-// its decision too, but made the whole 1B step 0.7% slower (same-box A/B).
+// combines them and the decision reduces one partial row per CU.  The VALU
+// version runs one 256-thread block per CU: four waves with two trips of
+// loads each already keep more bytes in flight than HBM needs (K = 8 bf16,
+// 51.4M elements: 150 us at one block per CU, 151 at two; 1.05M: 7.4 and
+// 9.0; K = 4 fp32 at 12.8M: 40.6 and 40.2, at 2.9M 11.2 and 11.7).
 template <int K>
-constexpr int pass1_threads() {
+constexpr int gram_threads() {
   return K <= 8 ? 256 : (K <= 16 ? 768 : 512);
 }
-
-template <int K, int kBlockThreads>
-__device__ void run_prev_decide(const PrevDecide& prev, const DecideParams& prm) {
-  __shared__ double gram[K * (K + 1) / 2];
-  __shared__ double scratch[kReduceLogical];
-  const DecideState st = load_decide_state<K>(prev.rec);
-  reduce_partials<K, kBlockThreads>(prev.partials, prev.rows, gram, scratch);
-  __syncthreads();
-  if (threadIdx.x < 64) decide<K>(gram, prev.rec, prm, st);
-}
-
 
 // Gram contributions of one 16-byte vector of every replica.
 template <int K, bool BF16>
@@ -468,93 +471,71 @@ __device__ __forceinline__ void gram_vector(double (&acc)[K * (K + 1) / 2], cons
 // clamps v, so that no load sits under a lane mask; a masked load makes the
 // compiler wait for the next trip's loads before computing this one.
 template <int K, bool BF16, bool NT>
-__device__ __forceinline__ void load_pass1(const float* theta, const ConstPtrs<K>& reps, int64_t v,
+__device__ __forceinline__ void load_gram(const float* theta, const ConstPtrs<K>& reps, int64_t v,
                                            float (&th)[Vec<BF16>::VE], u32x4 (&raw)[K]) {
   load_f32<Vec<BF16>::VE, NT>(theta, v, th);
 #pragma unroll
   for (int j = 0; j < K; ++j) raw[j] = ld16<NT>(reinterpret_cast<const u32x4*>(reps.p[j]) + v);
 }
 
-template <int K, bool BF16, bool NT>
-__global__ __launch_bounds__(pass1_threads<K>()) void pass1_gram_kernel(const float* __restrict__ theta,
-                                                              ConstPtrs<K> reps, int64_t nvec,
-                                                              int64_t n,
-                                                              double* __restrict__ partials,
-                                                              PrevDecide prev, DecideParams prm) {
-  constexpr int NP = K * (K + 1) / 2;
-  constexpr int VE = Vec<BF16>::VE;
-  const int first = prev.partials ? 1 : 0;  // block 0 may take the previous unit's decision
-  if (first && blockIdx.x == 0) {
-    run_prev_decide<K, pass1_threads<K>()>(prev, prm);
-    return;
+// Where each unit of a batch begins in the launch's items or blocks (unused
+// places hold INT32_MAX).  The array lies together in the kernel arguments,
+// so a block finds its unit from one wide scalar load.
+template <int U>
+struct FirstOf {
+  int32_t at[U];
+  __device__ __forceinline__ int unit_of(int x) const {
+    int w = 0;
+#pragma unroll
+    for (int i = 1; i < U; ++i) w += at[i] <= x ? 1 : 0;
+    return w;
   }
-  const int b = static_cast<int>(blockIdx.x) - first;  // this block's partial row
-  const int rows = static_cast<int>(gridDim.x) - first;
-#include "gram_rows_valu.inc"
-}
+};
 
-// The decisions of up to two earlier units of a round (prev1 only with
-// prev0), one after the other in the calling block.
+// One unit of a Gram launch.
 template <int K>
-__device__ void run_prev_decisions(const PrevDecide& prev0, const PrevDecide& prev1,
-                                   const DecideParams& prm) {
-  run_prev_decide<K, pass1_threads<K>()>(prev0, prm);
-  if (prev1.partials) {
-    __syncthreads();  // the first decision has read the shared Gram
-    run_prev_decide<K, pass1_threads<K>()>(prev1, prm);
-  }
-}
-
-// One unit of a two-unit Gram launch (rows == 0: none).
-template <int K>
-struct Pass1Part {
+struct GramUnit {
   const float* theta;
   ConstPtrs<K> reps;
   int64_t nvec;
   int64_t n;
-  double* partials;
-  int rows;
+  int64_t cut;       // first vector read through the cache (VALU pass)
+  double* partials;  // [rows][K(K+1)/2]
+  int32_t rows;
 };
 
-// Pass 1 of two consecutive units of a round in one launch (K <= 8).  Each
-// block writes its partial row of the first unit, then the same row of the
-// second, so each unit gets exactly the partials of its own launch (same
-// rows, same order).  The persistent grid then starts and drains once for
-// the two units instead of twice; that start and drain costs about 13 us
-// per launch whatever the unit size.  Block 0 may take the decisions of the
-// two units before them.  UNITS = 1 is the launch of one unit that takes
-// two such decisions.
-template <int K, bool BF16, bool NT, int UNITS>
-__global__ __launch_bounds__(pass1_threads<K>()) void pass1_gram_pair_kernel(Pass1Part<K> unit0,
-                                                                   Pass1Part<K> unit1,
-                                                                   PrevDecide prev0,
-                                                                   PrevDecide prev1,
-                                                                   DecideParams prm) {
+// The units of a Gram launch.  Its work items are the units' partial rows in
+// unit order; block b takes items b, b + gridDim.x, ...
+template <int K, int U>
+struct GramBatch {
+  FirstOf<U> first;  // items
+  GramUnit<K> u[U];
+  int32_t items;
+};
+
+template <int K, bool BF16, int U>
+__global__ __launch_bounds__(gram_threads<K>(), 2) void gram_kernel(GramBatch<K, U> batch) {
+  static_assert(K <= 8, "VALU Gram pass covers K <= 8");
   constexpr int NP = K * (K + 1) / 2;
   constexpr int VE = Vec<BF16>::VE;
-  const int first = prev0.partials ? 1 : 0;
-  if (first && blockIdx.x == 0) {
-    run_prev_decisions<K>(prev0, prev1, prm);
-    return;
-  }
-  const int b = static_cast<int>(blockIdx.x) - first;  // this block's partial row of each unit
 #pragma unroll 1
-  for (int w = 0; w < UNITS; ++w) {
-    const int rows = w == 0 ? unit0.rows : unit1.rows;
-    if (b >= rows) continue;
-    if (w == 1) __syncthreads();  // the first unit's block reduction has read red[]
-    const float* __restrict__ theta = w == 0 ? unit0.theta : unit1.theta;
+  for (int it = blockIdx.x; it < batch.items; it += gridDim.x) {
+    const int w = batch.first.unit_of(it);
+    const GramUnit<K>& unit = batch.u[w];
+    const float* __restrict__ theta = unit.theta;
     ConstPtrs<K> reps;
 #pragma unroll
-    for (int j = 0; j < K; ++j) reps.p[j] = w == 0 ? unit0.reps.p[j] : unit1.reps.p[j];
-    const int64_t nvec = w == 0 ? unit0.nvec : unit1.nvec;
-    const int64_t n = w == 0 ? unit0.n : unit1.n;
-    double* __restrict__ partials = w == 0 ? unit0.partials : unit1.partials;
+    for (int j = 0; j < K; ++j) reps.p[j] = unit.reps.p[j];
+    const int64_t nvec = unit.nvec, n = unit.n, cut = unit.cut;
+    const int rows = unit.rows, b = it - batch.first.at[w];
+    double* __restrict__ row_out = unit.partials + static_cast<int64_t>(b) * NP;
 #include "gram_rows_valu.inc"
+    if (U == 1) break;
+    __syncthreads();  // red[] is read before the next item writes it
   }
 }
 
-// Pass 1 for 8 < K <= 32: the Gram matrix sum_i d_i d_i^T over the unit's
+// The Gram pass for 8 < K <= 32: the Gram matrix sum_i d_i d_i^T over the unit's
 // elements is a rank-n update, and with K(K+1)/2 = 136 to 528 fp64 sums per
 // lane a VALU version runs out of registers.  It runs on the fp64 matrix
 // cores as v_mfma_f64_4x4x4f64, four independent 4x4x4 products per wave
@@ -648,34 +629,45 @@ __device__ __forceinline__ void gram_quad4(double (&acc)[Tiles4<K>::T], const u3
   }
 }
 
-template <int K, bool BF16, bool NT>
-__global__ __launch_bounds__(pass1_threads<K>()) void pass1_gram_mfma_kernel(const float* __restrict__ theta,
-                                                                   ConstPtrs<K> reps, int64_t nvec,
-                                                                   int64_t n,
-                                                                   double* __restrict__ partials,
-                                                                   PrevDecide prev,
-                                                                   DecideParams prm) {
+template <int K, bool BF16, bool NT, int U>
+__global__ __launch_bounds__(gram_threads<K>()) void gram_mfma_kernel(GramBatch<K, U> batch) {
   static_assert(K > 8 && K <= 32, "MFMA Gram pass covers 8 < K <= 32");
-  const int first = prev.partials ? 1 : 0;  // block 0 may take the previous unit's decision
-  if (first && blockIdx.x == 0) {
-    run_prev_decide<K, pass1_threads<K>()>(prev, prm);
-    return;
-  }
-  const int b = static_cast<int>(blockIdx.x) - first;  // this block's partial row
-  const int rows = static_cast<int>(gridDim.x) - first;
+  constexpr int NP = K * (K + 1) / 2;
+  constexpr int VE = Vec<BF16>::VE;
   constexpr int kDepth = kMfmaDepth<K>();
+#pragma unroll 1
+  for (int it = blockIdx.x; it < batch.items; it += gridDim.x) {
+    const int w = batch.first.unit_of(it);
+    const GramUnit<K>& unit = batch.u[w];
+    const float* __restrict__ theta = unit.theta;
+    ConstPtrs<K> reps;
+#pragma unroll
+    for (int j = 0; j < K; ++j) reps.p[j] = unit.reps.p[j];
+    const int64_t nvec = unit.nvec, n = unit.n;
+    const int rows = unit.rows, b = it - batch.first.at[w];
+    double* __restrict__ row_out = unit.partials + static_cast<int64_t>(b) * NP;
 #include "gram_rows_mfma.inc"
+    if (U == 1) break;
+    __syncthreads();  // gsh[] is read before the next item writes it
+  }
 }
+
 // ---------------------------------------------------------------- decide
 
-template <int K>
-__global__ __launch_bounds__(kDecideThreads) void decide_kernel(const double* __restrict__ partials,
-                                                                int rows, UnitRecord* __restrict__ rec,
-                                                                DecideParams prm) {
+// The units of a decision launch, one block each.
+template <int U>
+struct DecideBatch {
+  DecideDesc u[U];
+};
+
+template <int K, int U>
+__global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideBatch<U> batch, DecideParams prm) {
   __shared__ double gram[K * (K + 1) / 2];
-  __shared__ double scratch[kReduceLogical];
+  __shared__ double scratch[kDecideThreads];
+  const DecideDesc& unit = batch.u[U == 1 ? 0 : blockIdx.x];
+  UnitRecord* rec = unit.rec;
   const DecideState st = load_decide_state<K>(rec);
-  reduce_partials<K, kDecideThreads>(partials, rows, gram, scratch);
+  reduce_partials<K>(unit.partials, unit.rows, gram, scratch);
   __syncthreads();
   if (threadIdx.x < 64) decide<K>(gram, rec, prm, st);
 }
@@ -689,8 +681,8 @@ __global__ __launch_bounds__(kDecideThreads) void gram_reduce_kernel(const doubl
                                                                      int rows,
                                                                      double* __restrict__ gram_out) {
   __shared__ double gram[K * (K + 1) / 2];
-  __shared__ double scratch[kReduceLogical];
-  reduce_partials<K, kDecideThreads>(partials, rows, gram, scratch);
+  __shared__ double scratch[kDecideThreads];
+  reduce_partials<K>(partials, rows, gram, scratch);
   __syncthreads();
   for (int p = threadIdx.x; p < K * (K + 1) / 2; p += kDecideThreads) gram_out[p] = gram[p];
 }
@@ -707,7 +699,7 @@ __global__ __launch_bounds__(64) void decide_gram_kernel(const double* __restric
   decide<K>(gram, rec, prm, st);
 }
 
-// ---------------------------------------------------------------- pass 2
+// ----------------------------------------------------------- update pass
 
 // theta' and b' of one element, in fp64 from fp32 inputs (rounded once on store):
 //   Delta_hat = sum_j c_j (r_j - theta), c_j = beta w_j      (Eq. 3, 5)
@@ -722,7 +714,7 @@ __device__ __forceinline__ void nesterov(double dhat, float th, float b, double 
 
 // theta, b and the contributing replicas at vector v (nothing past the end).
 template <int K, bool BF16, bool NT>
-__device__ __forceinline__ void load_pass2(const float* theta, const float* mom,
+__device__ __forceinline__ void load_update(const float* theta, const float* mom,
                                            const u32x4* const (&src)[K], bool use, int64_t v,
                                            int64_t nvec, float (&th)[Vec<BF16>::VE],
                                            float (&b)[Vec<BF16>::VE], u32x4 (&raw)[K]) {
@@ -771,33 +763,59 @@ __device__ __forceinline__ void update_vector(float* theta, float* mom, const Mu
 // (update_pass_blocks_per_cu): fewer waves in flight serve this traffic
 // faster.  Blocks are taken from the unit's end; forward order measured the
 // same.
-template <int K, bool BF16, bool NT>
-__global__ __launch_bounds__(kPass2Threads) void pass2_update_kernel(float* __restrict__ theta,
-                                                                float* __restrict__ mom,
-                                                                MutPtrs<K> reps,
-                                                                const UnitRecord* __restrict__ rec,
-                                                                int64_t nvec, int64_t n, double lr,
-                                                                double rho) {
+template <int K>
+struct UpdateUnit {
+  float* theta;
+  float* mom;
+  MutPtrs<K> reps;
+  const UnitRecord* rec;
+  int64_t nvec;
+  int64_t n;
+  int32_t blocks;
+};
+
+template <int K, int U>
+struct UpdateBatch {
+  FirstOf<U> first;  // blocks
+  UpdateUnit<K> u[U];
+  double lr, rho;
+};
+
+template <int K, bool BF16, bool NT, int U>
+__global__ __launch_bounds__(kUpdateThreads) void update_kernel(UpdateBatch<K, U> batch) {
   constexpr int VE = Vec<BF16>::VE;
-  const int64_t v = static_cast<int64_t>(gridDim.x - 1 - blockIdx.x) * kPass2Threads + threadIdx.x;
+  const int blk = static_cast<int>(gridDim.x - 1 - blockIdx.x);  // from the batch's end
+  const int w = batch.first.unit_of(blk);
+  const int own = blk - batch.first.at[w];  // the unit's block
+  const UpdateUnit<K>& unit = batch.u[w];
+  float* __restrict__ theta = unit.theta;
+  float* __restrict__ mom = unit.mom;
+  const MutPtrs<K>& rep_args = unit.reps;
+  MutPtrs<K> reps;
+#pragma unroll
+  for (int j = 0; j < K; ++j) reps.p[j] = rep_args.p[j];
+  const UnitRecord* __restrict__ rec = unit.rec;
+  const int64_t nvec = unit.nvec, n = unit.n;
+  const double lr = batch.lr, rho = batch.rho;
+  const int64_t v = static_cast<int64_t>(own) * kUpdateThreads + threadIdx.x;
   const int64_t tail = nvec * VE + threadIdx.x;
-  const bool do_tail = blockIdx.x == 0 && tail < n;
-  constexpr bool kRecFresh = false;  // written by the decision of an earlier launch
+  const bool do_tail = own == unit.blocks - 1 && tail < n;
+  constexpr bool kRecInLds = false;  // written by the decision of an earlier launch
 
 #include "update_vector_at.inc"
 }
 
-// The access pattern of pass 2 with no arithmetic: the same grid, block
+// The access pattern of the update pass with no arithmetic: the same grid, block
 // order and 16-byte accesses, reading theta, b and all K replicas and
 // writing them all back (XOR with `flip`, zero at run time, keeps every
 // store), so its time is what this traffic costs with nothing computed.
-// Used to calibrate pass 2 against its own pattern, not by the method.
+// Used to calibrate the update pass against its own pattern, not by the method.
 template <int K, bool BF16, bool NT>
-__global__ __launch_bounds__(kPass2Threads) void update_pattern_probe_kernel(float* __restrict__ theta,
+__global__ __launch_bounds__(kUpdateThreads) void update_pattern_probe_kernel(float* __restrict__ theta,
                                                                             float* __restrict__ mom,
                                                                             MutPtrs<K> reps, int64_t nvec,
                                                                             uint32_t flip) {
-  const int64_t v = static_cast<int64_t>(gridDim.x - 1 - blockIdx.x) * kPass2Threads + threadIdx.x;
+  const int64_t v = static_cast<int64_t>(gridDim.x - 1 - blockIdx.x) * kUpdateThreads + threadIdx.x;
   if (v >= nvec) return;
   constexpr int H = Vec<BF16>::VE / 4;  // 16-byte vectors of theta (and of b) per replica vector
   u32x4 t[H], b[H], r[K];
@@ -819,93 +837,83 @@ __global__ __launch_bounds__(kPass2Threads) void update_pattern_probe_kernel(flo
   for (int j = 0; j < K; ++j) st16<NT>(reinterpret_cast<u32x4*>(reps.p[j]) + v, r[j] ^ flip);
 }
 
-// ------------------------------------------- single-block units of a round
+// ------------------------------------------------------ single-block units
 
 // A unit whose Gram pass is one block (at most 256 vectors) can be stepped
 // whole by one block: its Gram row, the decision and the update pass, one
-// after the other.  A round does that for up to kMaxSingleBlockUnits such
-// units in one small launch, which may also carry the previous unit's
-// decision (round_small_kernel).  The block runs the code of the unit's own
-// three launches (pass 1 with one row, the decision, pass 2 with one vector
-// per thread), included from the same fragments, so the results are the
-// same bit for bit.  The partial row and the record are written and read
-// back within the block: __syncthreads() orders global memory between the
-// waves of one work-group (they share the CU's L1); the partials are read
-// with non-temporal vector loads and the record with work-group-scope
-// atomic loads (rec_load), never through the scalar cache.
+// after the other, in one launch instead of three.  A launch takes up to
+// batch_units<K>() such units, a block each.  The block runs the code of the
+// three launches (the Gram pass with one row, the decision, the update with
+// one vector per thread), included from the same fragments, so the results
+// are the same bit for bit.  The row and the record stay in LDS: the block
+// copies the record in while its first loads are in flight, decides on it
+// there, and copies it back at the end.
 template <int K>
-struct SingleBlockUnit {
+struct SmallUnit {
   float* theta;
   float* mom;
-  void* reps[K];
-  double* partials;
+  MutPtrs<K> reps;
   UnitRecord* rec;
   int64_t n;
 };
 
-template <int K>
-struct SingleBlockUnits {
-  SingleBlockUnit<K> u[kMaxSingleBlockUnits];
-  int count;
+template <int K, int U>
+struct SmallBatch {
+  SmallUnit<K> u[U];
   double lr, rho;
 };
 
-template <int K, bool BF16, bool NT1, bool NT2, bool MFMA>
-__device__ void single_block_unit(const SingleBlockUnit<K>& su, const DecideParams& prm, double lr,
-                                  double rho) {
+template <int K, bool BF16, int U>
+__global__ __launch_bounds__(gram_threads<K>()) void small_step_kernel(SmallBatch<K, U> batch, DecideParams prm) {
+  constexpr int NP = K * (K + 1) / 2;
   constexpr int VE = Vec<BF16>::VE;
+  static_assert(sizeof(UnitRecord) % 16 == 0, "the record is copied in 16-byte vectors");
+  constexpr int kRecVectors = sizeof(UnitRecord) / 16;  // at most one per thread
+  static_assert(kRecVectors <= gram_threads<K>(), "one vector of the record per thread");
+  __shared__ double gram[NP];
+  __shared__ UnitRecord record;
+  const SmallUnit<K>& su = batch.u[U == 1 ? 0 : blockIdx.x];
   const int64_t n = su.n;
   const int64_t nvec = n / VE;
-  {  // pass 1: the unit's only Gram row
-    constexpr bool NT = NT1;
+  if (threadIdx.x < kRecVectors)
+    reinterpret_cast<u32x4*>(&record)[threadIdx.x] = reinterpret_cast<const u32x4*>(su.rec)[threadIdx.x];
+  {  // the Gram pass: the unit's only row
     const float* __restrict__ theta = su.theta;
     ConstPtrs<K> reps;
 #pragma unroll
-    for (int j = 0; j < K; ++j) reps.p[j] = su.reps[j];
-    double* __restrict__ partials = su.partials;
+    for (int j = 0; j < K; ++j) reps.p[j] = su.reps.p[j];
+    double* row_out = gram;
     const int b = 0, rows = 1;
-    if constexpr (MFMA) {
-      constexpr int kDepth = 2;  // a few trips at most: deeper prefetch only costs registers
+    if constexpr (K > 8) {
+      constexpr bool NT = kNTMfma;
+      constexpr int kDepth = 1;  // two trips at most: a second buffer only makes the code longer
 #include "gram_rows_mfma.inc"
     } else {
-      constexpr int NP = K * (K + 1) / 2;
+      const int64_t cut = 0;
 #include "gram_rows_valu.inc"
     }
   }
   __syncthreads();
-  run_prev_decide<K, pass1_threads<K>()>(PrevDecide{su.partials, 1, su.rec}, prm);
+  if (threadIdx.x < 64) decide<K>(gram, &record, prm, load_decide_state<K>(&record));
   __syncthreads();
-  {  // pass 2: one vector per thread (nvec <= 256 <= the block's threads)
-    constexpr bool NT = NT2;
+  if (threadIdx.x < kRecVectors)
+    reinterpret_cast<u32x4*>(su.rec)[threadIdx.x] = reinterpret_cast<const u32x4*>(&record)[threadIdx.x];
+  {  // the update: one vector per thread (nvec <= 256 <= the block's threads)
+    constexpr bool NT = kNT2;
     float* __restrict__ theta = su.theta;
     float* __restrict__ mom = su.mom;
+    const MutPtrs<K>& rep_args = su.reps;
     MutPtrs<K> reps;
 #pragma unroll
-    for (int j = 0; j < K; ++j) reps.p[j] = su.reps[j];
-    const UnitRecord* rec = su.rec;
+    for (int j = 0; j < K; ++j) reps.p[j] = rep_args.p[j];
+    const UnitRecord* rec = &record;
+    const double lr = batch.lr, rho = batch.rho;
     const int64_t v = threadIdx.x;
     const int64_t tail = nvec * VE + threadIdx.x;
     const bool do_tail = tail < n;
-    constexpr bool kRecFresh = true;  // written by this block's decision just above
+    constexpr bool kRecInLds = true;
 #include "update_vector_at.inc"
   }
-}
-
-// Block 0 takes the decisions of up to two earlier units when prev0.partials
-// is set; one block per single-block unit steps that unit.  The blocks have
-// the pass-1 kernel's size, so a unit's Gram row is the one its own pass 1
-// would write.
-template <int K, bool BF16, bool NT1, bool NT2, bool MFMA>
-__global__ __launch_bounds__(pass1_threads<K>()) void round_small_kernel(PrevDecide prev0, PrevDecide prev1,
-                                                               DecideParams prm,
-                                                               SingleBlockUnits<K> single) {
-  const int first = prev0.partials ? 1 : 0;
-  if (first && blockIdx.x == 0) {
-    run_prev_decisions<K>(prev0, prev1, prm);
-    return;
-  }
-  const int sb = static_cast<int>(blockIdx.x) - first;
-  if (sb < single.count) single_block_unit<K, BF16, NT1, NT2, MFMA>(single.u[sb], prm, single.lr, single.rho);
 }
 
 // ------------------------------------------------------ one-pass mean step
@@ -1081,11 +1089,11 @@ __global__ __launch_bounds__(kDecideThreads) void fused_finish_kernel(const Fini
 // ------------------------------------------------------------ copy probe
 
 template <int U, bool NT>
-__global__ __launch_bounds__(kThreads) void copy_kernel(u32x4* __restrict__ dst,
+__global__ __launch_bounds__(kCopyThreads) void copy_kernel(u32x4* __restrict__ dst,
                                                        const u32x4* __restrict__ src,
                                                        int64_t nvec) {
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
-  for (int64_t v = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; v < nvec; v += stride * U) {
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * kCopyThreads;
+  for (int64_t v = static_cast<int64_t>(blockIdx.x) * kCopyThreads + threadIdx.x; v < nvec; v += stride * U) {
     u32x4 x[U];
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -1100,111 +1108,87 @@ __global__ __launch_bounds__(kThreads) void copy_kernel(u32x4* __restrict__ dst,
 
 // ------------------------------------------------------------ launchers
 
-// Cache policy of the streaming kernels: both passes touch every byte once;
-// non-temporal accesses measured ~15% faster for pass 1 and ~5% for pass 2.
-constexpr bool kNT1 = true;
-constexpr bool kNTMfma = false;  // see pass1_gram_mfma_kernel
-constexpr bool kNT2 = true;
-
 namespace {
 
-// Pass 1 for this K: VALU accumulators up to K = 8, matrix cores above.
-template <int K, bool BF16>
-constexpr auto pass1_kernel() {
-  if constexpr (K <= 8)
-    return pass1_gram_kernel<K, BF16, kNT1>;
-  else
-    return pass1_gram_mfma_kernel<K, BF16, kNTMfma>;
+// Units of one launch (a batch of a round), bounded by the 4 KiB of kernel
+// arguments; a batch of one has kernels of its own, without the unit search.
+template <int K>
+constexpr int batch_units() {
+  return K <= 16 ? kMaxBatchUnits : kMaxBatchUnits / 2;
 }
 
-template <int K, bool BF16>
-hipError_t pass1_launch(int rows, const float* theta, const void* const* reps, int64_t n,
-                        double* partials, const double* prev_partials, int prev_rows,
-                        UnitRecord* prev_rec, const DecideParams& prm, hipStream_t stream) {
-  ConstPtrs<K> rp;
-  for (int j = 0; j < K; ++j) rp.p[j] = reps[j];
-  const int64_t nvec = n / Vec<BF16>::VE;
-  const PrevDecide prev{prev_partials, prev_rows, prev_rec};
-  const int blocks = rows + (prev_partials ? 1 : 0);
-  hipLaunchKernelGGL((pass1_kernel<K, BF16>()), dim3(blocks), dim3(pass1_threads<K>()), 0, stream, theta, rp,
-                     nvec, n, partials, prev, prm);
+template <int K, bool BF16, int U>
+hipError_t gram_launch_u(const UnitDesc* unit, int count, int max_blocks, hipStream_t stream) {
+  GramBatch<K, U> batch{};
+  std::fill_n(batch.first.at, U, INT32_MAX);
+  for (int i = 0; i < count; ++i) {
+    const UnitDesc& d = unit[i];
+    GramUnit<K>& g = batch.u[i];
+    g.theta = d.theta;
+    for (int j = 0; j < K; ++j) g.reps.p[j] = d.n > 0 ? d.reps[j] : nullptr;
+    g.nvec = d.n / Vec<BF16>::VE;
+    g.n = d.n;
+    g.cut = d.cut / Vec<BF16>::VE;
+    g.partials = d.partials;
+    g.rows = d.rows;
+    batch.first.at[i] = batch.items;
+    batch.items += d.rows;
+  }
+  const int blocks = U == 1 ? batch.items : std::min(batch.items, max_blocks);
+  if constexpr (K <= 8)
+    hipLaunchKernelGGL((gram_kernel<K, BF16, U>), dim3(blocks), dim3(gram_threads<K>()), 0, stream, batch);
+  else
+    hipLaunchKernelGGL((gram_mfma_kernel<K, BF16, kNTMfma, U>), dim3(blocks), dim3(gram_threads<K>()), 0, stream,
+                       batch);
   return hipGetLastError();
 }
 
-// Block 0's decisions: prev[0..nprev), nprev <= 2.
-inline void prev_decisions(const DecideDesc* prev, int nprev, PrevDecide& p0, PrevDecide& p1) {
-  p0 = nprev > 0 ? PrevDecide{prev[0].partials, prev[0].rows, prev[0].rec} : PrevDecide{nullptr, 0, nullptr};
-  p1 = nprev > 1 ? PrevDecide{prev[1].partials, prev[1].rows, prev[1].rec} : PrevDecide{nullptr, 0, nullptr};
+template <int K, bool BF16>
+hipError_t gram_launch(const UnitDesc* unit, int count, int max_blocks, hipStream_t stream) {
+  if (count < 1 || count > batch_units<K>()) return hipErrorInvalidValue;
+  return count == 1 ? gram_launch_u<K, BF16, 1>(unit, count, max_blocks, stream)
+                    : gram_launch_u<K, BF16, batch_units<K>()>(unit, count, max_blocks, stream);
 }
 
-template <int K, bool BF16>
-Pass1Part<K> pass1_part(const Pass1Desc* unit, int count, int i) {
-  Pass1Part<K> part{};
-  if (i >= count) return part;  // rows 0: no unit
-  const Pass1Desc& d = unit[i];
-  part.theta = d.theta;
-  for (int j = 0; j < K; ++j) part.reps.p[j] = d.n > 0 ? d.reps[j] : nullptr;
-  part.nvec = d.n / Vec<BF16>::VE;
-  part.n = d.n;
-  part.partials = d.partials;
-  part.rows = d.rows;
-  return part;
-}
-
-template <int K, bool BF16>
-hipError_t pass1_pair_launch(const Pass1Desc* unit, int count, const DecideDesc* prev, int nprev,
-                             const DecideParams& prm, hipStream_t stream) {
-  if constexpr (K > 8) {
-    return hipErrorInvalidValue;  // the matrix-core Gram pass runs one unit per launch
-  } else {
-    PrevDecide p0, p1;
-    prev_decisions(prev, nprev, p0, p1);
-    const Pass1Part<K> u0 = pass1_part<K, BF16>(unit, count, 0);
-    const Pass1Part<K> u1 = pass1_part<K, BF16>(unit, count, 1);
-    const int blocks = (nprev > 0 ? 1 : 0) + std::max(u0.rows, u1.rows);
-    if (count == 2)
-      hipLaunchKernelGGL((pass1_gram_pair_kernel<K, BF16, kNT1, 2>), dim3(blocks), dim3(pass1_threads<K>()),
-                         0, stream, u0, u1, p0, p1, prm);
-    else
-      hipLaunchKernelGGL((pass1_gram_pair_kernel<K, BF16, kNT1, 1>), dim3(blocks), dim3(pass1_threads<K>()),
-                         0, stream, u0, u1, p0, p1, prm);
-    return hipGetLastError();
-  }
-}
-
-template <int K, bool BF16>
-hipError_t round_small_launch(const DecideDesc* prev, int nprev, const DecideParams& prm,
-                              const SingleBlockDesc* unit, int count, double lr, double rho,
-                              hipStream_t stream) {
-  PrevDecide p0, p1;
-  prev_decisions(prev, nprev, p0, p1);
-  SingleBlockUnits<K> single{};
-  single.count = count;
-  single.lr = lr;
-  single.rho = rho;
+template <int K, bool BF16, int U>
+hipError_t small_step_launch_u(const UnitDesc* unit, int count, const DecideParams& prm, double lr, double rho,
+                               hipStream_t stream) {
+  SmallBatch<K, U> batch{};
+  batch.lr = lr;
+  batch.rho = rho;
   for (int i = 0; i < count; ++i) {
-    const SingleBlockDesc& d = unit[i];
-    single.u[i].theta = d.theta;
-    single.u[i].mom = d.mom;
-    for (int j = 0; j < K; ++j) single.u[i].reps[j] = d.n > 0 ? d.reps[j] : nullptr;
-    single.u[i].partials = d.partials;
-    single.u[i].rec = d.rec;
-    single.u[i].n = d.n;
+    const UnitDesc& d = unit[i];
+    batch.u[i].theta = d.theta;
+    batch.u[i].mom = d.mom;
+    for (int j = 0; j < K; ++j) batch.u[i].reps.p[j] = d.n > 0 ? d.reps[j] : nullptr;
+    batch.u[i].rec = d.rec;
+    batch.u[i].n = d.n;
   }
-  const int blocks = (nprev > 0 ? 1 : 0) + count;
-  if (blocks == 0) return hipSuccess;
-  constexpr bool kMfma = K > 8;
-  hipLaunchKernelGGL((round_small_kernel<K, BF16, kMfma ? kNTMfma : kNT1, kNT2, kMfma>), dim3(blocks),
-                     dim3(pass1_threads<K>()), 0, stream, p0, p1, prm, single);
+  hipLaunchKernelGGL((small_step_kernel<K, BF16, U>), dim3(count), dim3(gram_threads<K>()), 0, stream, batch, prm);
+  return hipGetLastError();
+}
+
+template <int K, bool BF16>
+hipError_t small_step_launch(const UnitDesc* unit, int count, const DecideParams& prm, double lr, double rho,
+                             hipStream_t stream) {
+  if (count < 1 || count > batch_units<K>()) return hipErrorInvalidValue;
+  return count == 1 ? small_step_launch_u<K, BF16, 1>(unit, count, prm, lr, rho, stream)
+                    : small_step_launch_u<K, BF16, batch_units<K>()>(unit, count, prm, lr, rho, stream);
+}
+
+template <int K, int U>
+hipError_t decide_launch_u(const UnitDesc* unit, int count, const DecideParams& prm, hipStream_t stream) {
+  DecideBatch<U> batch{};
+  for (int i = 0; i < count; ++i) batch.u[i] = {unit[i].partials, unit[i].rec, unit[i].rows};
+  hipLaunchKernelGGL((decide_kernel<K, U>), dim3(count), dim3(kDecideThreads), 0, stream, batch, prm);
   return hipGetLastError();
 }
 
 template <int K>
-hipError_t decide_launch(const double* partials, int rows, UnitRecord* rec, const DecideParams& prm,
-                         hipStream_t stream) {
-  hipLaunchKernelGGL((decide_kernel<K>), dim3(1), dim3(kDecideThreads), 0, stream, partials, rows, rec,
-                     prm);
-  return hipGetLastError();
+hipError_t decide_launch(const UnitDesc* unit, int count, const DecideParams& prm, hipStream_t stream) {
+  if (count < 1 || count > batch_units<K>()) return hipErrorInvalidValue;
+  return count == 1 ? decide_launch_u<K, 1>(unit, count, prm, stream)
+                    : decide_launch_u<K, batch_units<K>()>(unit, count, prm, stream);
 }
 
 template <int K>
@@ -1227,20 +1211,41 @@ hipError_t pattern_probe_launch(int blocks, int lds, float* theta, float* mom, v
   MutPtrs<K> rp;
   for (int j = 0; j < K; ++j) rp.p[j] = reps[j];
   const int64_t nvec = n / Vec<BF16>::VE;
-  hipLaunchKernelGGL((update_pattern_probe_kernel<K, BF16, kNT2>), dim3(blocks), dim3(kPass2Threads), lds, stream,
+  hipLaunchKernelGGL((update_pattern_probe_kernel<K, BF16, kNT2>), dim3(blocks), dim3(kUpdateThreads), lds, stream,
                      theta, mom, rp, nvec, 0u);
   return hipGetLastError();
 }
 
-template <int K, bool BF16>
-hipError_t pass2_launch(int blocks, int lds, float* theta, float* mom, void* const* reps,
-                        const UnitRecord* rec, int64_t n, double lr, double rho, hipStream_t stream) {
-  MutPtrs<K> rp;
-  for (int j = 0; j < K; ++j) rp.p[j] = reps[j];
-  const int64_t nvec = n / Vec<BF16>::VE;
-  hipLaunchKernelGGL((pass2_update_kernel<K, BF16, kNT2>), dim3(blocks), dim3(kPass2Threads), lds, stream, theta,
-                     mom, rp, rec, nvec, n, lr, rho);
+template <int K, bool BF16, int U>
+hipError_t update_launch_u(const UnitDesc* unit, int count, int lds, double lr, double rho, hipStream_t stream) {
+  UpdateBatch<K, U> batch{};
+  std::fill_n(batch.first.at, U, INT32_MAX);
+  batch.lr = lr;
+  batch.rho = rho;
+  int blocks = 0;
+  for (int i = 0; i < count; ++i) {
+    const UnitDesc& d = unit[i];
+    UpdateUnit<K>& u = batch.u[i];
+    u.theta = d.theta;
+    u.mom = d.mom;
+    for (int j = 0; j < K; ++j) u.reps.p[j] = d.n > 0 ? d.reps[j] : nullptr;
+    u.rec = d.rec;
+    u.nvec = d.n / Vec<BF16>::VE;
+    u.n = d.n;
+    batch.first.at[i] = blocks;
+    u.blocks = d.update_blocks;
+    if (d.update_blocks > INT32_MAX - blocks) return hipErrorInvalidValue;
+    blocks += d.update_blocks;
+  }
+  hipLaunchKernelGGL((update_kernel<K, BF16, kNT2, U>), dim3(blocks), dim3(kUpdateThreads), lds, stream, batch);
   return hipGetLastError();
+}
+
+template <int K, bool BF16>
+hipError_t update_launch(const UnitDesc* unit, int count, int lds, double lr, double rho, hipStream_t stream) {
+  if (count < 1 || count > batch_units<K>()) return hipErrorInvalidValue;
+  return count == 1 ? update_launch_u<K, BF16, 1>(unit, count, lds, lr, rho, stream)
+                    : update_launch_u<K, BF16, batch_units<K>()>(unit, count, lds, lr, rho, stream);
 }
 
 // Vectors per thread of the one-pass kernel (measured: two 16-byte vectors
@@ -1268,40 +1273,21 @@ hipError_t fused_finish_launch(const FinishEntry* table, int units, hipStream_t 
   return hipGetLastError();
 }
 
-template <typename Kern>
-int occupancy(Kern kernel, int threads) {
-  int blocks = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, kernel, threads, 0) != hipSuccess ||
-      blocks < 1)
-    blocks = 1;
-  return blocks;
-}
-
 template <int K>
 struct Launchers {
-  static hipError_t pass1(bool bf16, int rows, const float* theta, const void* const* reps, int64_t n,
-                          double* partials, const double* prev_partials, int prev_rows, UnitRecord* prev_rec,
-                          const DecideParams& prm, hipStream_t stream) {
-    return bf16 ? pass1_launch<K, true>(rows, theta, reps, n, partials, prev_partials, prev_rows, prev_rec, prm,
-                                        stream)
-                : pass1_launch<K, false>(rows, theta, reps, n, partials, prev_partials, prev_rows, prev_rec, prm,
-                                         stream);
+  static hipError_t gram(bool bf16, const UnitDesc* unit, int count, int max_blocks, hipStream_t stream) {
+    return bf16 ? gram_launch<K, true>(unit, count, max_blocks, stream)
+                : gram_launch<K, false>(unit, count, max_blocks, stream);
   }
-  static hipError_t pass1_pair(bool bf16, const Pass1Desc* unit, int count, const DecideDesc* prev, int nprev,
-                               const DecideParams& prm, hipStream_t stream) {
-    return bf16 ? pass1_pair_launch<K, true>(unit, count, prev, nprev, prm, stream)
-                : pass1_pair_launch<K, false>(unit, count, prev, nprev, prm, stream);
+  static hipError_t small_step(bool bf16, const UnitDesc* unit, int count, const DecideParams& prm, double lr,
+                               double rho, hipStream_t stream) {
+    return bf16 ? small_step_launch<K, true>(unit, count, prm, lr, rho, stream)
+                : small_step_launch<K, false>(unit, count, prm, lr, rho, stream);
   }
-  static hipError_t round_small(bool bf16, const DecideDesc* prev, int nprev, const DecideParams& prm,
-                                const SingleBlockDesc* unit, int count, double lr, double rho,
-                                hipStream_t stream) {
-    return bf16 ? round_small_launch<K, true>(prev, nprev, prm, unit, count, lr, rho, stream)
-                : round_small_launch<K, false>(prev, nprev, prm, unit, count, lr, rho, stream);
-  }
-  static hipError_t pass2(bool bf16, int blocks, int lds, float* theta, float* mom, void* const* reps,
-                          const UnitRecord* rec, int64_t n, double lr, double rho, hipStream_t stream) {
-    return bf16 ? pass2_launch<K, true>(blocks, lds, theta, mom, reps, rec, n, lr, rho, stream)
-                : pass2_launch<K, false>(blocks, lds, theta, mom, reps, rec, n, lr, rho, stream);
+  static hipError_t update(bool bf16, const UnitDesc* unit, int count, int lds, double lr, double rho,
+                           hipStream_t stream) {
+    return bf16 ? update_launch<K, true>(unit, count, lds, lr, rho, stream)
+                : update_launch<K, false>(unit, count, lds, lr, rho, stream);
   }
   static hipError_t pattern_probe(bool bf16, int blocks, int lds, float* theta, float* mom, void* const* reps,
                                   int64_t n, hipStream_t stream) {
@@ -1314,10 +1300,6 @@ struct Launchers {
     return bf16 ? fused_mean_launch<K, true>(rows, lds, theta, mom, reps, partials, rec, n, lr, rho, stream)
                 : fused_mean_launch<K, false>(rows, lds, theta, mom, reps, partials, rec, n, lr, rho, stream);
   }
-  static int pass1_blocks_per_cu(bool bf16) {
-    return bf16 ? occupancy(pass1_kernel<K, true>(), pass1_threads<K>())
-                : occupancy(pass1_kernel<K, false>(), pass1_threads<K>());
-  }
 };
 
 // The set of K, or nullptr when K lies outside this object's range (the
@@ -1326,11 +1308,9 @@ template <int K>
 const KernelSet* set_if_in_range() {
   if constexpr (K >= EDIT_K_FIRST && K <= EDIT_K_LAST) {
     static constexpr KernelSet set{
-        &Launchers<K>::pass1,          &Launchers<K>::pass1_pair,     &Launchers<K>::round_small,
-        &decide_launch<K>,             &gram_reduce_launch<K>,        &decide_gram_launch<K>,
-        &Launchers<K>::pass2,          &Launchers<K>::fused_mean,     &fused_finish_launch<K>,
-        &Launchers<K>::pass1_blocks_per_cu, &Launchers<K>::pattern_probe, fused_v<K, true>(),
-        fused_v<K, false>()};
+        &Launchers<K>::gram,   &decide_launch<K>,          &Launchers<K>::small_step, &gram_reduce_launch<K>,
+        &decide_gram_launch<K>, &Launchers<K>::update,      &Launchers<K>::fused_mean, &fused_finish_launch<K>,
+        &Launchers<K>::pattern_probe, batch_units<K>(), fused_v<K, true>(), fused_v<K, false>()};
     return &set;
   } else {
     return nullptr;
@@ -1360,7 +1340,7 @@ constexpr int kUnrollCopy = 1;
 constexpr bool kNTCopy = false;
 
 hipError_t launch_copy(void* dst, const void* src, int64_t nbytes, int blocks, hipStream_t stream) {
-  hipLaunchKernelGGL((copy_kernel<kUnrollCopy, kNTCopy>), dim3(blocks), dim3(kThreads), 0, stream,
+  hipLaunchKernelGGL((copy_kernel<kUnrollCopy, kNTCopy>), dim3(blocks), dim3(kCopyThreads), 0, stream,
                      reinterpret_cast<u32x4*>(dst), reinterpret_cast<const u32x4*>(src), nbytes / 16);
   return hipGetLastError();
 }

@@ -1,0 +1,96 @@
+"""Launches that step several units, and where their Gram input is cached (GPU).
+
+A round steps consecutive units in batches of three launches and units of one
+Gram block (at most 256 vectors) in launches of their own; the partial rows
+of a unit do not depend on the batch, so every schedule must give the bits of
+unit-by-unit edit_outer_step_layer calls.  The Gram pass reads the end of its
+input through the cache and the rest non-temporally, two loops of the same
+sums, so a step over a unit that crosses that line must give the bits of the
+Gram and apply calls, which stream all of it.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2412_07210_amd import EditOuter, OuterConfig
+
+pytestmark = pytest.mark.gpu
+
+DEV = torch.device("cuda:0")
+
+
+def _inputs(cfg, gen):
+    units = []
+    for n in cfg.layer_numel:
+        theta = torch.empty(n, device=DEV).normal_(0.0, 0.02, generator=gen)
+        mom = torch.empty(n, device=DEV).normal_(0.0, 1e-3, generator=gen)
+        reps = [(theta + (j + 1) * 1e-3 * torch.empty(n, device=DEV).normal_(0.0, 1.0, generator=gen))
+                .to(cfg.torch_dtype) for j in range(cfg.num_workers)]
+        units.append((theta, mom, reps))
+    return units
+
+
+def _copy(units):
+    return [(t.clone(), b.clone(), [r.clone() for r in reps]) for t, b, reps in units]
+
+
+def _same(a, b, what):
+    for u, (x, y) in enumerate(zip(a, b)):
+        assert torch.equal(x[0], y[0]) and torch.equal(x[1], y[1]), f"{what}: unit {u}"
+        assert all(torch.equal(p, q) for p, q in zip(x[2], y[2])), f"{what}: unit {u} replicas"
+
+
+def _same_state(a, b, n, what):
+    for u in range(n):
+        x, y = a.state_get(u), b.state_get(u)
+        for f in ("norm", "ema_mean", "ema_std", "weight", "anomalous"):
+            assert np.array_equal(getattr(x, f), getattr(y, f)), f"{what}: unit {u} {f}"
+        assert (x.synced_norm, x.clip_coef, x.round) == (y.synced_norm, y.clip_coef, y.round), f"{what}: unit {u}"
+
+
+# vectors per unit: single blocks (0..256), the first of two rows (257), one
+# row per CU and one vector more (65,536, 65,537), and 18 units of more than
+# one block, which no batch holds; "ragged" elements follow the last vector
+_MIXES = {
+    "all small": [0, 1, 255, 256, 3, 17, 256, 2, 9, 100, 31, 64, 65, 5, 7, 8, 250, 11, 256],
+    "full batch": [257 + 16 * i for i in range(16)],
+    "past a batch": [300, 257, 65_537, 400, 999, 1000, 258, 513, 65_536, 270, 301, 800, 4097, 600, 512, 2049, 700,
+                     9_999],
+    "mixed": [1000, 3, 70_000, 0, 257, 256, 1, 5000],
+}
+
+
+@pytest.mark.parametrize("K,dtype", [(1, "f32"), (4, "f32"), (8, "bf16"), (9, "bf16"), (16, "f32"), (17, "bf16"),
+                                     (32, "bf16")])
+@pytest.mark.parametrize("mix", list(_MIXES))
+def test_round_in_batches_matches_unit_by_unit(mix, K, dtype):
+    ve = 8 if dtype == "bf16" else 4
+    sizes = [v * ve + i % ve for i, v in enumerate(_MIXES[mix])]
+    cfg = OuterConfig(K, sizes, dtype, clip_threshold=0.05)
+    gen = torch.Generator(device=DEV).manual_seed(K)
+    one = _inputs(cfg, gen)
+    all_ = _copy(one)
+    with EditOuter(cfg, DEV) as a, EditOuter(cfg, DEV) as b:
+        for _ in range(2):  # the second round starts from equal replicas
+            for u, unit in enumerate(one):
+                a.step_layer(u, *unit)
+            b.step_round(all_)
+        torch.cuda.synchronize()
+        _same(one, all_, f"{mix} K={K} {dtype}")
+        _same_state(a, b, len(sizes), f"{mix} K={K} {dtype}")
+
+
+@pytest.mark.parametrize("K,dtype,n", [(8, "bf16", 12_000_005), (4, "f32", 9_000_003), (2, "bf16", 25_000_001),
+                                       (1, "f32", 25_000_002)])
+def test_step_across_the_cached_end_matches_the_streamed_gram(K, dtype, n):
+    cfg = OuterConfig(K, [n], dtype)
+    gen = torch.Generator(device=DEV).manual_seed(n)
+    one = _inputs(cfg, gen)
+    two = _copy(one)
+    with EditOuter(cfg, DEV) as a, EditOuter(cfg, DEV) as b:
+        a.step_layer(0, *one[0])
+        theta, mom, reps = two[0]
+        b.apply_layer(0, b.gram_layer(0, theta, reps), theta, mom, reps)
+        torch.cuda.synchronize()
+        _same(one, two, f"K={K} {dtype} n={n}")
+        _same_state(a, b, 1, f"K={K} {dtype} n={n}")
