@@ -61,15 +61,22 @@ hipError_t launch_update(int K, bool bf16, const UnitDesc* unit, int count, int 
 // limit) 14.31-14.36 ms, 4 per CU 13.91-14.01, 3 per CU 13.84-13.87;
 // one-wave blocks, 6 per CU 13.56-13.60 ms, against 13.60-13.68 at 4 or 5,
 // 13.72-13.73 at 7 and 14.00-14.02 at 8.  Six one-wave blocks per CU also
-// gave the shortest 350M, 7B half-shard and A-EDiT K = 16 rounds.
-int update_pass_blocks_per_cu(int K) {
-  (void)K;
-  return 6;
+// gave the shortest 350M, 7B half-shard and A-EDiT K = 16 rounds.  With few
+// workers a block has fewer loads in flight (K + 2 with fp32 replicas, K + 4
+// with bf16) and more blocks are needed; measured on one box at 6, 8 and 16
+// blocks per CU: K = 1 fp32, 28.3M elements 200, 180 and 162 us a step; K = 2
+// bf16, nine of 28.3M 1,443, 1,442 and 1,371; K = 2 fp32, 5.8M 63, 59 and 59;
+// K = 4 fp32, nine of 2.9M 323, 295 and 303; but K = 4 bf16, nine of 12.8M
+// 839, 862 and 850, K = 3 bf16, 51.4M 325, 329 and 331, K = 6 fp32, 12.8M
+// 200, 200 and 203.
+int update_pass_blocks_per_cu(int K, bool bf16) {
+  if (K <= 2) return 16;
+  return K <= 4 && !bf16 ? 8 : 6;
 }
 
-int update_pass_lds(int K, int lds_per_cu) {
+int update_pass_lds(int K, bool bf16, int lds_per_cu) {
   // the largest multiple of 256 bytes that still lets that many blocks fit
-  return lds_per_cu > 0 ? (lds_per_cu / update_pass_blocks_per_cu(K)) & ~255 : 0;
+  return lds_per_cu > 0 ? (lds_per_cu / update_pass_blocks_per_cu(K, bf16)) & ~255 : 0;
 }
 
 int fused_vectors_per_thread(int K, bool bf16) {

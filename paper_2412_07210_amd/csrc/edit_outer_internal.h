@@ -126,8 +126,8 @@ hipError_t launch_update(int K, bool bf16, const UnitDesc* unit, int count, int 
                          hipStream_t stream);
 // Update-pass blocks resident per CU, and the dynamic LDS per block that
 // caps them there given the CU's LDS bytes.
-int update_pass_blocks_per_cu(int K);
-int update_pass_lds(int K, int lds_per_cu);
+int update_pass_blocks_per_cu(int K, bool bf16);
+int update_pass_lds(int K, bool bf16, int lds_per_cu);
 // One-pass mean step (no penalty components): `rows` blocks of
 // fused_vectors_per_thread(K, bf16) * kFusedThreads vectors each, leaving
 // rows x (K+1) norm partials (each block's K+1 sums contiguous) and the unit marked; then one block per entry

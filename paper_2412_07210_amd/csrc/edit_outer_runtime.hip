@@ -315,7 +315,7 @@ edit_status_t edit_outer_init(const edit_outer_config_t* cfg, edit_outer_t* out)
       delete h;
       return fail_hip(e, "hipDeviceGetAttribute(LDS per CU)");
     }
-    h->pass2_lds = update_pass_lds(K, lds_per_cu);
+    h->pass2_lds = update_pass_lds(K, cfg->replica_dtype == EDIT_BF16, lds_per_cu);
     h->fused_lds = one_pass_lds(K, cfg->replica_dtype == EDIT_BF16, lds_per_cu);
   }
   h->noalloc = noalloc;
