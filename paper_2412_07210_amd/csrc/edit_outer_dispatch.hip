@@ -84,17 +84,18 @@ int fused_vectors_per_thread(int K, bool bf16) {
   return s ? (bf16 ? s->fused_vectors_bf16 : s->fused_vectors_f32) : 1;
 }
 
-// The one-pass kernel streams the same 2K + 4 buffers as the update pass.
-// With bf16 replicas (two 16-byte vectors per thread) and one-wave blocks,
-// six resident blocks per CU measured best at the 1B shape (rocprofv3, A/B
-// runs on one box): 435 us per unit against 438-442 at five or seven blocks
-// and 441 for 128-thread blocks at four per CU (the earlier shape, itself
-// 10.64-10.73 ms per round against 11.02-11.07 uncapped).  One vector per
-// thread took 474-484 us: each block's closing reduction and partial row
-// then cover half as much data.  Other cases keep the occupancy their
-// registers give.
+// The one-pass kernel streams the same 2K + 4 buffers as the update pass, in
+// one-wave blocks, two 16-byte vectors per thread with bf16 replicas up to
+// K = 16 and one otherwise (one took 474-484 us per 51.4M bf16 unit at K = 8
+// against 435: each block's closing reduction and partial row then cover half
+// as much data).  Resident blocks per CU, us per round on one box at the
+// cap's best and uncapped: K = 8 bf16, four of 28.3M 968 at five, 982 at six,
+// 1,025; K = 8 fp32, four of 12.8M 690 at eight, 713 at six, 788; K = 16
+// fp32, three of 5M 383 at five, 453; K = 16 bf16, two of 9.4M 301 and 310;
+// K = 24 bf16 406 at five, 441; K = 4 bf16, four of 12.8M 323 at six, 338;
+// K = 4 fp32, six of 2.9M 180 at eight, 183; K = 2 no gain at any.
 int one_pass_lds(int K, bool bf16, int lds_per_cu) {
-  const int blocks = bf16 && K <= 16 ? 6 : 0;
+  const int blocks = K <= 2 ? 0 : (!bf16 && K <= 8 ? 8 : (K <= 4 ? 6 : 5));
   return blocks > 0 && lds_per_cu > 0 ? (lds_per_cu / blocks) & ~255 : 0;
 }
 
@@ -106,9 +107,9 @@ hipError_t launch_fused_mean(int K, bool bf16, int rows, int lds, float* theta, 
            : hipErrorInvalidValue;
 }
 
-hipError_t launch_fused_finish(int K, const FinishEntry* table, int units, hipStream_t stream) {
+hipError_t launch_fused_finish(int K, const FinishEntry* table, int units, bool fold, hipStream_t stream) {
   const KernelSet* s = kernels_for(K);
-  return s ? s->fused_finish(table, units, stream) : hipErrorInvalidValue;
+  return s ? s->fused_finish(table, units, fold, stream) : hipErrorInvalidValue;
 }
 
 hipError_t launch_pattern_probe(int K, bool bf16, int blocks, int lds, float* theta, float* mom, void* const* reps,

@@ -38,11 +38,12 @@ struct alignas(16) UnitRecord {
 
 // Where the one-pass record reduction of a unit finds its inputs.
 struct FinishEntry {
-  const double* partials;
+  double* partials;
   UnitRecord* rec;
   int32_t rows;
-  int32_t pad;
+  int32_t slice;  // rows per slice that the fold launch sums first (1: none)
 };
+constexpr int kFoldSlices = 64;  // at most, per unit
 
 struct DecideParams {
   double alpha, delta, phi, eps;
@@ -91,7 +92,7 @@ struct KernelSet {
                        hipStream_t stream);
   hipError_t (*fused_mean)(bool bf16, int rows, int lds, float* theta, float* mom, void* const* reps,
                            double* partials, UnitRecord* rec, int64_t n, double lr, double rho, hipStream_t stream);
-  hipError_t (*fused_finish)(const FinishEntry* table, int units, hipStream_t stream);
+  hipError_t (*fused_finish)(const FinishEntry* table, int units, bool fold, hipStream_t stream);
   hipError_t (*pattern_probe)(bool bf16, int blocks, int lds, float* theta, float* mom, void* const* reps,
                               int64_t n, hipStream_t stream);
   int batch_units;
@@ -139,7 +140,8 @@ int one_pass_lds(int K, bool bf16, int lds_per_cu);
 hipError_t launch_fused_mean(int K, bool bf16, int rows, int lds, float* theta, float* mom,
                              void* const* reps, double* partials, UnitRecord* rec, int64_t n,
                              double lr, double rho, hipStream_t stream);
-hipError_t launch_fused_finish(int K, const FinishEntry* table, int units, hipStream_t stream);
+// `fold`: some unit has slices to sum first.
+hipError_t launch_fused_finish(int K, const FinishEntry* table, int units, bool fold, hipStream_t stream);
 hipError_t launch_copy(void* dst, const void* src, int64_t nbytes, int blocks,
                        hipStream_t stream);
 // The update pass's loads and stores (whole vectors only) with no arithmetic.

@@ -1022,6 +1022,56 @@ __global__ __launch_bounds__(kFusedThreads) void fused_mean_kernel(float* __rest
   if (b == 0 && threadIdx.x == 0) rec->finish_pending = 1;
 }
 
+// The sums over rows r0, r0 + step, ... (`count` of them) of a one-pass
+// unit's partials [rows][K+1], per column in a fixed order, in tot[K+1]
+// (shared memory).  Thread t always reads column t % NV and a wave's loads
+// are contiguous when step is 1; U loads per thread are in flight at a time,
+// and the threads' sums are added per column in thread order.
+template <int K>
+__device__ __forceinline__ void sum_rows(const double* partials, int r0, int step, int count, double* part,
+                                         double* tot) {
+  constexpr int NV = K + 1;
+  constexpr int T = kDecideThreads / NV;  // rows read at a time
+  constexpr int U = 8;
+  const int t = threadIdx.x, c = t % NV;
+  double s = 0.0;
+  if (t < NV * T) {
+    for (int r = t / NV; r < count; r += T * U) {
+      double v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int at = r + u * T;
+        v[u] = at < count ? partials[(r0 + static_cast<int64_t>(at) * step) * NV + c] : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) s += v[u];
+    }
+  }
+  part[t] = s;
+  __syncthreads();
+  if (t < NV) {
+    double x = 0.0;
+    for (int k = t; k < NV * T; k += NV) x += part[k];
+    tot[t] = x;
+  }
+}
+
+// Large one-pass units: block (s, u) sums slice s of unit u's rows into the
+// slice's first row, so that the one block that makes the unit's record has
+// at most kFoldSlices rows left.  By itself that block read every row of a
+// 28.3M-element unit (27,651 of nine sums) at the rate of one CU: 36 us for
+// a round's units, where the two launches take 8.8 and 6.8.
+template <int K>
+__global__ __launch_bounds__(kDecideThreads) void fused_fold_kernel(const FinishEntry* __restrict__ table) {
+  const FinishEntry ent = table[blockIdx.y];
+  const int r0 = blockIdx.x * ent.slice;
+  if (ent.slice < 2 || r0 >= ent.rows || !ent.rec->finish_pending) return;  // block-uniform
+  __shared__ double part[kDecideThreads];
+  __shared__ double tot[K + 1];
+  sum_rows<K>(ent.partials, r0, 1, min(ent.slice, ent.rows - r0), part, tot);
+  if (threadIdx.x < K + 1) ent.partials[static_cast<int64_t>(r0) * (K + 1) + threadIdx.x] = tot[threadIdx.x];
+}
+
 // The records of one-pass steps: G_j and ||Delta_bar|| from each unit's
 // partials (in a fixed order), w_j = 1/K, beta = 1.  One block per unit of
 // `table`; units whose fused pass has not run since their last record are
@@ -1033,39 +1083,9 @@ __global__ __launch_bounds__(kDecideThreads) void fused_finish_kernel(const Fini
   const FinishEntry ent = table[blockIdx.x];
   UnitRecord* rec = ent.rec;
   if (!rec->finish_pending) return;  // block-uniform
-  const double* partials = ent.partials;
-  const int rows = ent.rows;
-  constexpr int NV = K + 1;
-  // The partials are rows x NV contiguous doubles.  Thread t reads the flat
-  // array at t, t + S, t + 2S, ... with S a multiple of NV, so it always
-  // reads column t % NV and a wave's loads are contiguous; U loads per
-  // thread are in flight at a time.  The S threads' sums are then added per
-  // column in thread order (a fixed order).
-  constexpr int S = NV * (kDecideThreads / NV);
-  constexpr int U = 16;
   __shared__ double part[kDecideThreads];
-  __shared__ double tot[NV];
-  const int64_t total = static_cast<int64_t>(rows) * NV;
-  double s = 0.0;
-  if (threadIdx.x < S) {
-    for (int64_t i = threadIdx.x; i < total; i += int64_t(S) * U) {
-      double v[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int64_t idx = i + int64_t(u) * S;
-        v[u] = idx < total ? partials[idx] : 0.0;
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) s += v[u];
-    }
-  }
-  part[threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.x < NV) {
-    double t = 0.0;
-    for (int k = threadIdx.x; k < S; k += NV) t += part[k];
-    tot[threadIdx.x] = t;
-  }
+  __shared__ double tot[K + 1];
+  sum_rows<K>(ent.partials, 0, ent.slice, (ent.rows + ent.slice - 1) / ent.slice, part, tot);
   __syncthreads();
   if (threadIdx.x < K) {
     rec->norm[threadIdx.x] = sqrt(tot[threadIdx.x]);
@@ -1268,7 +1288,12 @@ hipError_t fused_mean_launch(int rows, int lds, float* theta, float* mom, void* 
 }
 
 template <int K>
-hipError_t fused_finish_launch(const FinishEntry* table, int units, hipStream_t stream) {
+hipError_t fused_finish_launch(const FinishEntry* table, int units, bool fold, hipStream_t stream) {
+  if (fold) {
+    hipLaunchKernelGGL((fused_fold_kernel<K>), dim3(kFoldSlices, units), dim3(kDecideThreads), 0, stream, table);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL((fused_finish_kernel<K>), dim3(units), dim3(kDecideThreads), 0, stream, table);
   return hipGetLastError();
 }

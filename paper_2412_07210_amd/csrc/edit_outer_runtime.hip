@@ -145,6 +145,15 @@ namespace {
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// Rows per slice of a one-pass unit's fold launch (1: one block sums them
+// all).  Up to 1 MiB of partials one block takes less time than the extra
+// launch saves (28.3M elements: 0.7 MB at K = 2 281 us a round of two without
+// and 286 with it, 2.0 MB at K = 8 1,003 and 981 a round of four).
+int32_t fold_slice(int32_t rows, int K) {
+  const int64_t doubles = static_cast<int64_t>(rows) * (K + 1);
+  return doubles > 131072 ? static_cast<int32_t>(ceil_div(rows, kFoldSlices)) : 1;
+}
+
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 edit_status_t check_device(const edit_outer* h) {
@@ -367,7 +376,7 @@ edit_status_t edit_outer_init(const edit_outer_config_t* cfg, edit_outer_t* out)
   if (e == hipSuccess && h->one_pass) {
     std::vector<FinishEntry> table(cfg->num_layers);
     for (int l = 0; l < cfg->num_layers; ++l)
-      table[l] = {h->units[l].partials, h->units[l].rec, h->units[l].rows, 0};
+      table[l] = {h->units[l].partials, h->units[l].rec, h->units[l].rows, fold_slice(h->units[l].rows, K)};
     h->finish_table = reinterpret_cast<FinishEntry*>(h->arena + table_off);
     e = hipMemcpy(h->finish_table, table.data(), sizeof(FinishEntry) * table.size(),
                   hipMemcpyHostToDevice);
@@ -566,7 +575,9 @@ struct Enqueue {
     return e == hipSuccess ? EDIT_OK : fail_hip(e, "one-pass launch");
   }
   edit_status_t records(int32_t first, int32_t units) {
-    hipError_t e = launch_fused_finish(K, h->finish_table + first, units, s);
+    bool fold = false;
+    for (int32_t l = first; l < first + units; ++l) fold = fold || fold_slice(h->units[l].rows, K) > 1;
+    hipError_t e = launch_fused_finish(K, h->finish_table + first, units, fold, s);
     return e == hipSuccess ? EDIT_OK : fail_hip(e, "record launch");
   }
   edit_status_t finish(int32_t layer) {

@@ -12,7 +12,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2412_07210_amd import EditOuter, OuterConfig
+from paper_2412_07210_amd import ONE_PASS, EditOuter, OuterConfig
 
 pytestmark = pytest.mark.gpu
 
@@ -94,3 +94,29 @@ def test_step_across_the_cached_end_matches_the_streamed_gram(K, dtype, n):
         torch.cuda.synchronize()
         _same(one, two, f"K={K} {dtype} n={n}")
         _same_state(a, b, 1, f"K={K} {dtype} n={n}")
+
+
+@pytest.mark.parametrize("K,dtype,rows", [(16, "f32", 7710), (16, "f32", 7711), (32, "bf16", 3972), (24, "bf16", 9999)])
+def test_one_pass_norms_on_both_sides_of_the_fold(K, dtype, rows):
+    """Past 131,072 doubles of partial rows a one-pass unit's rows are summed
+    in slices first: G_j and ||Delta_bar|| of a step alone and of a round,
+    against 64-bit torch sums (n * 2^-52 relative, all terms positive)."""
+    per_row = 64 * (8 if dtype == "bf16" else 4) * (2 if dtype == "bf16" and K <= 16 else 1)
+    n = (rows - 1) * per_row + 3
+    cfg = OuterConfig(K, [n, 1000, n], dtype, flags=ONE_PASS)
+    gen = torch.Generator(device=DEV).manual_seed(rows)
+    units = _inputs(cfg, gen)
+    want = []
+    for t, _, reps in units:
+        d = torch.stack([r.double() - t.double() for r in reps])
+        want.append((d.square().sum(1).sqrt(), d.mean(0).square().sum().sqrt()))
+        del d
+    with EditOuter(cfg, DEV) as h:
+        h.step_layer(0, *units[0])
+        h.step_round(units[1:], layers=[1, 2])
+        for u, (g, bar) in enumerate(want):
+            st = h.state_get(u)
+            m = cfg.layer_numel[u]
+            assert np.allclose(st.norm, g.cpu().numpy(), rtol=(m + 1) * 2.0 ** -52, atol=0.0), f"unit {u}"
+            assert abs(st.synced_norm - float(bar)) <= (m + K) * 2.0 ** -52 * float(bar), f"unit {u}"
+            assert st.round == 1
