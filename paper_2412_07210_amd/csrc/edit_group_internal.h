@@ -13,6 +13,7 @@ namespace edit {
 constexpr int kGroupThreads = 256;        // streaming passes
 constexpr int kGroupNormVecs = 2;        // 16-byte vectors per thread of the norm pass
 constexpr int kGroupUpdateThreads = 128;  // the update pass
+constexpr int kGroupUpdateBlocks = 4;     // of them resident per CU
 constexpr int kGroupOneBlock = 1024;      // the one-block reductions
 
 // Device-resident state and decision of one unit on one rank.
@@ -50,7 +51,7 @@ hipError_t launch_group_dbar(int rows, const GroupRecord* rec, const float* dbar
                              double* partials, hipStream_t stream);
 hipError_t launch_group_clip(const double* partials, int rows, GroupRecord* rec, const GroupParams& prm,
                              hipStream_t stream);
-hipError_t launch_group_update(bool bf16, int blocks, const GroupRecord* rec, const float* dbar,
+hipError_t launch_group_update(bool bf16, int blocks, int lds, const GroupRecord* rec, const float* dbar,
                                float* theta, float* mom, void* rep, int64_t n, double lr, double rho,
                                hipStream_t stream);
 int group_dbar_blocks_per_cu();

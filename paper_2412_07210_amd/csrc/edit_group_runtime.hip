@@ -67,6 +67,7 @@ struct edit_group {
   std::vector<int64_t> numel;
   int rank = 0;
   int device = 0;
+  int update_lds = 0;  // dynamic LDS per update-pass block (occupancy cap)
   char* arena = nullptr;
   std::vector<GUnit> units;
 };
@@ -171,6 +172,9 @@ edit_status_t edit_group_init(const edit_outer_config_t* cfg, int32_t rank, edit
     return gfail(EDIT_EINVAL, "rank must be in 0.." + std::to_string(cfg->num_workers - 1));
   int dev = 0, num_cu = 0;
   GROUP_TRY(current_gfx950(&dev, &num_cu));
+  int lds_per_cu = 0;
+  hipError_t e = hipDeviceGetAttribute(&lds_per_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev);
+  if (e != hipSuccess) return gfail_hip(e, "hipDeviceGetAttribute(LDS per CU)");
 
   edit_group* h = new (std::nothrow) edit_group;
   if (!h) return gfail(EDIT_ENOMEM, "host allocation failed");
@@ -179,6 +183,7 @@ edit_status_t edit_group_init(const edit_outer_config_t* cfg, int32_t rank, edit
   h->cfg.layer_numel = h->numel.data();
   h->rank = rank;
   h->device = dev;
+  h->update_lds = (lds_per_cu / kGroupUpdateBlocks) & ~255;
   const bool bf16 = cfg->replica_dtype == EDIT_BF16;
   const int ve = bf16 ? 8 : 4;
   const int cap_dbar = num_cu * group_dbar_blocks_per_cu();
@@ -202,7 +207,7 @@ edit_status_t edit_group_init(const edit_outer_config_t* cfg, int32_t rank, edit
     offs[l] = total;
     total += rec_bytes + ((sizeof(double) * (u.rows_norm + u.rows_dbar) + 255) & ~size_t(255));
   }
-  hipError_t e = hipMalloc(reinterpret_cast<void**>(&h->arena), total);
+  e = hipMalloc(reinterpret_cast<void**>(&h->arena), total);
   if (e != hipSuccess) {
     h->arena = nullptr;
     destroy_group_units(h);
@@ -291,7 +296,7 @@ edit_status_t edit_group_apply(edit_group_t h, int32_t layer, const float* dbar,
   hipError_t e = launch_group_dbar(u.rows_dbar, u.rec, dbar, n, u.part_dbar, s);
   if (e == hipSuccess) e = launch_group_clip(u.part_dbar, u.rows_dbar, u.rec, prm, s);
   if (e == hipSuccess && n > 0)
-    e = launch_group_update(bf16, u.blocks_up, u.rec, dbar, theta, momentum, replica, n, h->cfg.outer_lr,
+    e = launch_group_update(bf16, u.blocks_up, h->update_lds, u.rec, dbar, theta, momentum, replica, n, h->cfg.outer_lr,
                             h->cfg.momentum, s);
   if (e != hipSuccess) return gfail_hip(e, "group apply launch");
   u.has_state = true;
