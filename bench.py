@@ -315,7 +315,7 @@ def measure_secondary(torch, np, name: str, steps: int, warmup: int, seed: int, 
                 "unit": "GB/s", "frac": round(achieved / PEAK_HBM_GBPS, 4), "avg_launch_ms": round(ms, 5),
                 "sampled_launches": len(samples)}
 
-    pass1_name = "pass1_gram_mfma_kernel" if K > 8 else "pass1_gram_kernel"
+    pass1_name = "gram_mfma_kernel" if K > 8 else "gram_kernel"
     out = {
         "workload": f"{wl.name}: {wl.description}", "units": wl.num_units, "num_workers": K,
         "replica_dtype": wl.replica_dtype, "steps": steps, "warmup": warmup,
@@ -324,9 +324,8 @@ def measure_secondary(torch, np, name: str, steps: int, warmup: int, seed: int, 
         "value": round(value, 2), "unit": "GB/s", "pct_peak_hbm": round(100 * value / PEAK_HBM_GBPS, 2),
         "gbps_on_min_bytes": round(min_bytes / (total_ms * 1e-3) / 1e9, 2),
         "masked_workers_total": masked, "rollbacks_total": rollbacks,
-        "pass1": roof(p1, pass1_name + " (its unit's Gram pass; in a round up to K = 8 it also "
-                          "carries earlier units' decisions)"),
-        "pass2": roof(p2, "pass2_update_kernel"),
+        "pass1": roof(p1, pass1_name + " and decide_kernel (a sampled unit's own launches)"),
+        "pass2": roof(p2, "update_kernel"),
     }
     # the dominant kernel by time: the update pass (twice pass 1's bytes)
     out["dominant"] = "pass2" if sum(m for m, _ in p2) >= sum(m for m, _ in p1) else "pass1"
@@ -344,7 +343,7 @@ def _profile_cmds(variant: str) -> dict:
     return {
         "tag": tag, "suffix": sfx,
         "trace": f"rocprofv3 --kernel-trace --stats -f csv -d <out>/prof_trace{sfx} -o {tag} -- "
-                 f"python bench.py{flag}",
+                 f"python bench.py --no-cpu-baseline --secondary 0{flag}",
         "fetch": f"rocprofv3 --pmc FETCH_SIZE -f csv -d <out>/prof_fetch{sfx} -o {tag} -- "
                  f"python bench.py --steps 2 --warmup 1 --no-cpu-baseline --profile-every 0 --secondary 0 "
                  f"--update-probe 0{flag}",
@@ -354,28 +353,32 @@ def _profile_cmds(variant: str) -> dict:
     }
 
 
-# The two-unit Gram launch and the one-unit launch that takes two earlier
-# units' decisions are one kernel template (its last argument is the unit
-# count); they are told apart here.
-PAIR2, PAIR1 = "pass1_gram_pair_kernel<..., 2>", "pass1_gram_pair_kernel<..., 1>"
-PASS1_KINDS = ("pass1_gram_kernel", "pass1_gram_mfma_kernel", PAIR2, PAIR1)
-UNITS_PER_LAUNCH = {PAIR2: 2}
-
-SHORT = {"pass1_gram_kernel": "pass1", PAIR2: "pass1_pair", PAIR1: "pass1_pair1", "decide_kernel": "decide",
-         "pass2_update_kernel": "pass2", "fused_mean_kernel": "fused", "fused_finish_kernel": "finish",
-         "update_pattern_probe_kernel": "probe"}
+KINDS = ("gram_kernel", "gram_mfma_kernel", "decide_kernel", "update_kernel", "small_step_kernel",
+         "fused_mean_kernel", "fused_fold_kernel", "fused_finish_kernel", "update_pattern_probe_kernel",
+         "copy_kernel")
+BATCHED = ("gram_kernel", "gram_mfma_kernel", "decide_kernel")  # launches followed by their batch's update_kernel
+SHORT = {"gram_kernel": "pass1", "decide_kernel": "decide", "update_kernel": "pass2", "fused_mean_kernel": "fused",
+         "fused_fold_kernel": "fold", "fused_finish_kernel": "finish", "update_pattern_probe_kernel": "probe"}
 
 
 def _kernel_kind(name: str) -> str:
-    m = re.search(r"pass1_gram_pair_kernel<[^>]*, (\d+)>", name)
-    if m:
-        return PAIR2 if m.group(1) == "2" else PAIR1
-    for kind in ("pass1_gram_kernel", "pass1_gram_mfma_kernel", "decide_kernel", "pass2_update_kernel",
-                 "round_small_kernel", "fused_mean_kernel", "fused_finish_kernel", "update_pattern_probe_kernel",
-                 "copy_kernel"):
-        if kind in name:
+    for kind in KINDS:  # as a whole name: decide_gram_kernel and group_update_kernel are others
+        if re.search(r"(?<![a-z_])" + kind, name):
             return kind
     return ""
+
+
+def _batch_grids(disp):
+    """Per dispatch (kind, grid) in stream order, the grid of the update pass
+    of its batch: one work-item per 16-byte replica vector of the batch's
+    units.  The Gram pass and the decision come just before that launch; any
+    other kernel keeps its own grid."""
+    out, nxt = [], None
+    for kind, grid in reversed(disp):
+        if kind == "update_kernel":
+            nxt = grid
+        out.append(nxt if kind in BATCHED and nxt else grid)
+    return out[::-1]
 
 
 def summarize_trace_by_grid(out_dir: str, name: str) -> str:
@@ -388,62 +391,51 @@ def summarize_trace_by_grid(out_dir: str, name: str) -> str:
     wl = synth.get(name)
     tag = name.replace("-", "_")  # file-name form of the workload name
     K, R = wl.num_workers, wl.replica_bytes
-    sizes = sorted(set(wl.layer_numel))
     groups, regs = {}, {}
-    spans = []  # (start, end, kind) of every dispatch, for the gaps between kernels
+    spans = []  # (start, end, kind, grid) of every dispatch
     with open(os.path.join(out_dir, f"prof_trace_{tag}", f"{tag}_kernel_trace.csv")) as f:
         for row in csv.DictReader(f):
             kind = _kernel_kind(row["Kernel_Name"])
-            spans.append((int(row["Start_Timestamp"]), int(row["End_Timestamp"]), kind))
+            grid = int(row.get("Grid_Size") or row.get("Grid_Size_X"))
+            spans.append((int(row["Start_Timestamp"]), int(row["End_Timestamp"]), kind, grid))
             if not kind or kind == "copy_kernel":
                 continue
-            grid = int(row.get("Grid_Size") or row.get("Grid_Size_X"))
-            dur = int(row["End_Timestamp"]) - int(row["Start_Timestamp"])
-            groups.setdefault((kind, grid), []).append(dur)
             regs[kind] = (row.get("VGPR_Count", "?"), row.get("Accum_VGPR_Count", "?"),
                           row.get("LDS_Block_Size", "?"))
+    spans.sort()
+    for (t0, t1, kind, _), grid in zip(spans, _batch_grids([(k, g) for _, _, k, g in spans])):
+        if kind and kind != "copy_kernel":
+            groups.setdefault((kind, grid), []).append(t1 - t0)
 
     ve = 8 if wl.replica_dtype == "bf16" else 4  # elements per 16-byte replica vector
 
-    def unit_of(kind, grid):
-        for n in sizes:
-            nvec = -(-n // ve)
-            if kind in ("pass2_update_kernel", "update_pattern_probe_kernel") and -(-nvec // 64) * 64 == grid:
-                return n
-            tpb = 768 if kind == "pass1_gram_mfma_kernel" else 256  # threads per Gram-pass block
-            if kind in PASS1_KINDS and -(-nvec // 256) >= grid // tpb - 1:
-                return n
-        return None
+    def elements(kind, grid):  # of the launch's batch, each unit rounded up to 64 vectors
+        return grid * ve if kind in (*BATCHED, "update_kernel", "update_pattern_probe_kernel") else None
 
-    # a two-unit launch counts two units of the size its grid matches (the
-    # workloads that pair units have units of one size)
     def algo(kind, n):
-        if kind in PASS1_KINDS:
-            return UNITS_PER_LAUNCH.get(kind, 1) * n * (4 + K * R)
-        if kind == "update_pattern_probe_kernel":  # every replica, whole vectors only
-            return (n // (16 // R)) * (16 // R) * (16 + 2 * K * R)
-        return n * (16 + 2 * K * R) if kind == "pass2_update_kernel" else None
+        if kind in ("gram_kernel", "gram_mfma_kernel"):
+            return n * (4 + K * R)
+        return n * (16 + 2 * K * R) if kind in ("update_kernel", "update_pattern_probe_kernel") else None
     lines = [f"# Kernel durations by unit size: {wl.description}", "",
              "Command (from the repository root; `<out>` = the directory the profiler wrote to):", "",
              f"    rocprofv3 --kernel-trace --stats -f csv -d <out>/prof_trace_{tag} -o {tag} -- "
              f"python bench.py --config {name} --steps 10 --warmup 5 --no-cpu-baseline --secondary 0", "",
              f"Summarised with `python bench.py --summarize-trace <out> {name}` (groups the trace's "
-             "dispatches by kernel and grid size).", "",
-             "| kernel | grid work-items | unit elements | calls | avg us | min us | max us | "
+             "dispatches by kernel and by the elements of the launch's batch of units, taken from its update "
+             "pass's grid).", "",
+             "| kernel | work-items of the update pass (or own) | batch elements | calls | avg us | min us | max us | "
              "algorithmic bytes | GB/s at avg |", "|---|---|---|---|---|---|---|---|---|"]
     for (kind, grid) in sorted(groups, key=lambda kg: (kg[0], -kg[1])):
         d = groups[(kind, grid)]
         avg = sum(d) / len(d)
-        n = unit_of(kind, grid)
+        n = elements(kind, grid)
         b = algo(kind, n) if n else None
         gbps = f"{b / (avg * 1e-9) / 1e9:.1f}" if b else "-"
         lines.append(f"| {kind} | {grid} | {n if n else '-'} | {len(d)} | {avg / 1e3:.1f} | "
                      f"{min(d) / 1e3:.1f} | {max(d) / 1e3:.1f} | {b if b else '-'} | {gbps} |")
     # idle time between consecutive dispatches that are both steps of the
     # method (the stream's dependency latency; torch and copy kernels excluded)
-    spans.sort()
-    ours = {*PASS1_KINDS, "decide_kernel", "pass2_update_kernel", "round_small_kernel", "fused_mean_kernel",
-            "fused_finish_kernel"}
+    ours = set(KINDS) - {"update_pattern_probe_kernel", "copy_kernel"}
     pairs = [(a[2], b[2], b[0] - a[1]) for a, b in zip(spans, spans[1:]) if a[2] in ours and b[2] in ours]
     gaps = sorted(g for _, _, g in pairs)
     if gaps:
@@ -477,15 +469,21 @@ def summarize_profiles(out_dir: str, bench_json: str, variant: str = "two-pass")
     cmds = _profile_cmds(variant)
     tag, sfx = cmds["tag"], cmds["suffix"]
     one = variant == "one-pass"
-    kinds = ("fused_mean_kernel", "fused_finish_kernel") if one else \
-        ("pass1_gram_kernel", PAIR2, PAIR1, "decide_kernel", "pass2_update_kernel", "update_pattern_probe_kernel")
-    dominant = "fused_mean_kernel" if one else "pass2_update_kernel"
+    kinds = ("fused_mean_kernel", "fused_fold_kernel", "fused_finish_kernel") if one else \
+        ("gram_kernel", "decide_kernel", "update_kernel", "update_pattern_probe_kernel")
+    dominant = "fused_mean_kernel" if one else "update_kernel"
     wl = synth.get(DEFAULT_WORKLOAD)
     n, K, R = wl.layer_numel[0], wl.num_workers, wl.replica_bytes
-    algo = {"pass1_gram_kernel": n * (4 + K * R), PAIR2: 2 * n * (4 + K * R), PAIR1: n * (4 + K * R),
-            "pass2_update_kernel": n * (8 + K * R + 8 + K * R),
+    algo = {"gram_kernel": n * (4 + K * R), "update_kernel": n * (8 + K * R + 8 + K * R),
             "update_pattern_probe_kernel": n * (8 + K * R + 8 + K * R),
             "fused_mean_kernel": n * (8 + K * R + 8 + K * R)}
+    unit_grid = -(-(-(-n // (16 // R))) // 64) * 64  # update-pass work-items of one unit
+
+    def units_of(disp):
+        """Units per launch of every dispatch (kind, grid) in stream order."""
+        return [g // unit_grid if k in (*BATCHED, "update_kernel") else 1
+                for (k, _), g in zip(disp, _batch_grids(disp))]
+
     title = "one-pass mean step (no penalty components)" if one else "outer step"
     prof_dir = os.path.join(ROOT, "profiles")
     os.makedirs(prof_dir, exist_ok=True)
@@ -493,65 +491,60 @@ def summarize_profiles(out_dir: str, bench_json: str, variant: str = "two-pass")
     with open(bench_json) as f:
         bench = json.load(f)
 
-    # kernel durations of the headline workload: the default run also steps
-    # the secondary workloads afterwards, the first of them with fp32
-    # replicas, so the headline's dispatches are those before the first
-    # method kernel built for fp32 replicas (template argument false)
+    # kernel durations by units per launch
     disp = []
     with open(os.path.join(out_dir, f"prof_trace{sfx}", f"{tag}_kernel_trace.csv")) as f:
         for row in csv.DictReader(f):
             kind = _kernel_kind(row["Kernel_Name"])
             if kind and kind != "copy_kernel":
                 disp.append((int(row["Start_Timestamp"]), int(row["End_Timestamp"]), kind,
-                             bool(re.search(r"<\d+, false|ILi\d+ELb0E", row["Kernel_Name"]))))
+                             int(row.get("Grid_Size") or row.get("Grid_Size_X"))))
     disp.sort()
-    cutoff = next((t0 for t0, _, _, f32 in disp if f32), None)
     durs = {}
-    for t0, t1, kind, _ in disp:
-        if cutoff is None or t0 < cutoff:
-            durs.setdefault(kind, []).append(t1 - t0)
+    for (t0, t1, kind, _), u in zip(disp, units_of([(d[2], d[3]) for d in disp])):
+        durs.setdefault((kind, u), []).append(t1 - t0)
     stats = {k: {"Calls": len(v), "AverageNs": sum(v) / len(v), "MinNs": min(v), "MaxNs": max(v)}
              for k, v in durs.items()}
     lines = [f"# Kernel durations: 1B K=8 {title} (24 units x 51,384,320, bf16 replicas)", "",
              "Command (from the repository root; `<out>` = the directory the profiler wrote to):", "",
              "    " + cmds["trace"], "",
-             "Dispatches of the headline workload only (those before the secondary workloads' first "
-             "kernel); summarised with `python bench.py --summarize-profiles <out> <bench json>`.", "",
-             "| kernel | calls | avg us | min us | max us | algorithmic bytes | GB/s at avg |",
-             "|---|---|---|---|---|---|---|"]
-    for kind in kinds:
-        st = stats.get(kind)
-        if not st:
+             "Summarised with `python bench.py --summarize-profiles <out> <bench json>`.", "",
+             "| kernel | units per launch | calls | avg us | min us | max us | algorithmic bytes | GB/s at avg |",
+             "|---|---|---|---|---|---|---|---|"]
+    for kind, u in sorted(stats, key=lambda ku: (kinds.index(ku[0]) if ku[0] in kinds else len(kinds), ku[1])):
+        if kind not in kinds:
             continue
-        b = algo.get(kind)
+        st = stats[kind, u]
+        b = algo[kind] * u if kind in algo else None
         gbps = f"{b / (st['AverageNs'] * 1e-9) / 1e9:.1f}" if b else "-"
-        lines.append(f"| {kind} | {int(st['Calls'])} | {st['AverageNs'] / 1e3:.1f} | "
+        lines.append(f"| {kind} | {u} | {int(st['Calls'])} | {st['AverageNs'] / 1e3:.1f} | "
                      f"{st['MinNs'] / 1e3:.1f} | {st['MaxNs'] / 1e3:.1f} | {b if b else '-'} | {gbps} |")
     rl = bench.get("roofline") or {}
-    if dominant in stats and rl:
+    if (dominant, 1) in stats and rl:
         ours = rl["avg_launch_ms"] * 1e3
-        prof = stats[dominant]["AverageNs"] / 1e3
+        prof = stats[dominant, 1]["AverageNs"] / 1e3
         lines += ["", f"bench.py's own HIP-event average for {dominant} in the traced run "
                   f"(sampled units, its JSON line's roofline.avg_launch_ms): {ours:.1f} us; "
-                  f"rocprofv3 over all launches of the same run: {prof:.1f} us "
+                  f"rocprofv3 over all one-unit launches of the same run: {prof:.1f} us "
                   f"({100 * (ours - prof) / prof:+.1f}%)."]
     with open(os.path.join(prof_dir, f"{name}_kernel_trace_stats.md"), "w") as f:
         f.write("\n".join(lines) + "\n")
 
     # HBM counters, calibrated on the 2 GiB copy probe of the same run
     def counters(which):
-        per = {}
         with open(os.path.join(out_dir, f"prof_{which}{sfx}", f"{tag}_counter_collection.csv")) as f:
-            for row in csv.DictReader(f):
-                kind = _kernel_kind(row["Kernel_Name"])
-                if kind:
-                    per.setdefault((kind, int(row["Grid_Size"])), []).append(float(row["Counter_Value"]))
+            rows = sorted((int(r["Dispatch_Id"]), _kernel_kind(r["Kernel_Name"]), int(r["Grid_Size"]),
+                           float(r["Counter_Value"])) for r in csv.DictReader(f))
+        rows = [r[1:] for r in rows if r[1]]
+        per = {}  # kind -> (counter, units) of each launch
+        for (kind, _, value), u in zip(rows, units_of([(k, g) for k, g, _ in rows])):
+            per.setdefault(kind, []).append((value, u))
         return per
 
     fetch, write = counters("fetch"), counters("write")
     copy_bytes = 2 << 30
-    copy_fetch = max(v for (k, g), vals in fetch.items() if k == "copy_kernel" for v in vals)
-    copy_write = max(v for (k, g), vals in write.items() if k == "copy_kernel" for v in vals)
+    copy_fetch = max(v for v, _ in fetch["copy_kernel"])
+    copy_write = max(v for v, _ in write["copy_kernel"])
     fetch_scale = copy_bytes / (copy_fetch * 1024)
     write_scale = copy_bytes / (copy_write * 1024)
     try:  # keep the other variant's entries when they were taken on this source
@@ -571,22 +564,21 @@ def summarize_profiles(out_dir: str, bench_json: str, variant: str = "two-pass")
              f"Calibration on the plain 2 GiB copy kernel in the same runs: FETCH_SIZE reads "
              f"{copy_fetch:.0f} KiB and WRITE_SIZE {copy_write:.0f} KiB for 2,097,152 KiB moved each "
              f"way, so FETCH_SIZE is scaled by {fetch_scale:.4f} and WRITE_SIZE by {write_scale:.4f}.", "",
-             "| kernel | dispatches | FETCH_SIZE KiB | WRITE_SIZE KiB | scaled bytes/launch | "
-             "algorithmic bytes | ratio | GB/s on measured bytes at trace avg |",
+             "Per unit: a launch's counters divided by its units.", "",
+             "| kernel | dispatches | units | FETCH_SIZE KiB | WRITE_SIZE KiB | scaled bytes/unit | "
+             "algorithmic bytes | ratio |",
              "|---|---|---|---|---|---|---|---|"]
     for kind in kinds:
-        fv = [v for (k, g), vals in fetch.items() if k == kind for v in vals]
-        wv = [v for (k, g), vals in write.items() if k == kind for v in vals]
+        fv, wv = fetch.get(kind), write.get(kind)
         if not fv or not wv:
             continue
-        f_kib, w_kib = sum(fv) / len(fv), sum(wv) / len(wv)
+        units = sum(u for _, u in fv)
+        f_kib, w_kib = sum(v for v, _ in fv) / units, sum(v for v, _ in wv) / sum(u for _, u in wv)
         traffic = f_kib * 1024 * fetch_scale + w_kib * 1024 * write_scale
         b = algo.get(kind)
         ratio = f"{traffic / b:.4f}" if b else "-"
-        st = stats.get(kind)
-        gbps = f"{traffic / (st['AverageNs'] * 1e-9) / 1e9:.1f}" if st else "-"
-        lines.append(f"| {kind} | {len(fv)} | {f_kib:.1f} | {w_kib:.1f} | {traffic:.4e} | "
-                     f"{b if b else '-'} | {ratio} | {gbps} |")
+        lines.append(f"| {kind} | {len(fv)} | {units} | {f_kib:.1f} | {w_kib:.1f} | {traffic:.4e} | "
+                     f"{b if b else '-'} | {ratio} |")
         short = SHORT[kind]
         out[f"{short}_bytes_per_launch"] = round(traffic)
         out[f"{short}_fetch_kib"] = round(f_kib, 1)
@@ -787,7 +779,7 @@ def summarize_sq_counters(out_dir: str) -> str:
     for k in SQ_PASSES:
         with open(os.path.join(out_dir, f"prof_sq_{k}", "sq_counter_collection.csv")) as f:
             for row in csv.DictReader(f):
-                if "pass1_gram_mfma_kernel" not in row["Kernel_Name"] or int(row["Grid_Size"]) < 100_000:
+                if "gram_mfma_kernel" not in row["Kernel_Name"] or int(row["Grid_Size"]) < 100_000:
                     continue  # the unit's launches, not the gains' single blocks
                 vals.setdefault(row["Counter_Name"], []).append(float(row["Counter_Value"]))
     avg = {c: sum(v) / len(v) for c, v in vals.items()}
@@ -796,7 +788,7 @@ def summarize_sq_counters(out_dir: str) -> str:
              "Commands (from the repository root; `<out>` = the directory the profiler wrote to):", ""]
     lines += ["    " + c for c in sq_commands().values()]
     lines += ["", f"Summarised with `python bench.py --summarize-sq-counters <out>`; per-dispatch averages over "
-              f"{min(len(v) for v in vals.values())} dispatches of pass1_gram_mfma_kernel on the unit.", "",
+              f"{min(len(v) for v in vals.values())} dispatches of gram_mfma_kernel on the unit.", "",
               "| counter | per dispatch | per element |", "|---|---|---|"]
     for c in SQ_PASSES["a"] + SQ_PASSES["b"]:
         if c in avg:
@@ -1105,7 +1097,7 @@ def main(argv=None) -> int:
         achieved = per_launch / (avg_ms * 1e-3) / 1e9
         traffic = measured_traffic("pass2", wl.name)
         result["roofline"] = {
-            "kernel": "pass2_update_kernel (fused average + clip + Nesterov + write-back)",
+            "kernel": "update_kernel (fused average + clip + Nesterov + write-back)",
             "bound": "hbm",
             "achieved": round(achieved, 2),
             "peak": PEAK_HBM_GBPS,
