@@ -100,16 +100,16 @@ int one_pass_lds(int K, bool bf16, int lds_per_cu) {
 }
 
 hipError_t launch_fused_mean(int K, bool bf16, int rows, int lds, float* theta, float* mom, void* const* reps,
-                             double* partials, UnitRecord* rec, int64_t n, double lr, double rho,
+                             double* partials, int64_t n, double lr, double rho,
                              hipStream_t stream) {
   const KernelSet* s = kernels_for(K);
-  return s ? s->fused_mean(bf16, rows, lds, theta, mom, reps, partials, rec, n, lr, rho, stream)
+  return s ? s->fused_mean(bf16, rows, lds, theta, mom, reps, partials, n, lr, rho, stream)
            : hipErrorInvalidValue;
 }
 
-hipError_t launch_fused_finish(int K, const FinishEntry* table, int units, bool fold, hipStream_t stream) {
+hipError_t launch_fused_finish(int K, const FinishDesc* unit, int count, int sliced, hipStream_t stream) {
   const KernelSet* s = kernels_for(K);
-  return s ? s->fused_finish(table, units, fold, stream) : hipErrorInvalidValue;
+  return s ? s->fused_finish(unit, count, sliced, stream) : hipErrorInvalidValue;
 }
 
 hipError_t launch_pattern_probe(int K, bool bf16, int blocks, int lds, float* theta, float* mom, void* const* reps,

@@ -32,18 +32,19 @@ struct alignas(16) UnitRecord {
   int32_t use_deltas;       // 0: no worker has a non-zero coefficient
   int32_t z_tested;
   int32_t stepped;          // at least one step or state_set happened
-  int32_t finish_pending;   // one-pass mode: partials written, record not yet made
   uint8_t anomalous[kMaxK];
 };
 
-// Where the one-pass record reduction of a unit finds its inputs.
-struct FinishEntry {
-  double* partials;
+// A unit whose one-pass record a launch makes.
+struct FinishDesc {
+  const double* partials;  // [rows][K+1]
+  double* sums;            // [kFoldSlices][K+1], written by the fold launch (sliced units only)
   UnitRecord* rec;
   int32_t rows;
   int32_t slice;  // rows per slice that the fold launch sums first (1: none)
 };
-constexpr int kFoldSlices = 64;  // at most, per unit
+constexpr int kFoldSlices = 64;      // at most, per unit
+constexpr int kMaxFinishUnits = 64;  // units of one record launch
 
 struct DecideParams {
   double alpha, delta, phi, eps;
@@ -91,8 +92,8 @@ struct KernelSet {
   hipError_t (*update)(bool bf16, const UnitDesc* unit, int count, int lds, double lr, double rho,
                        hipStream_t stream);
   hipError_t (*fused_mean)(bool bf16, int rows, int lds, float* theta, float* mom, void* const* reps,
-                           double* partials, UnitRecord* rec, int64_t n, double lr, double rho, hipStream_t stream);
-  hipError_t (*fused_finish)(const FinishEntry* table, int units, bool fold, hipStream_t stream);
+                           double* partials, int64_t n, double lr, double rho, hipStream_t stream);
+  hipError_t (*fused_finish)(const FinishDesc* unit, int count, int sliced, hipStream_t stream);
   hipError_t (*pattern_probe)(bool bf16, int blocks, int lds, float* theta, float* mom, void* const* reps,
                               int64_t n, hipStream_t stream);
   int batch_units;
@@ -131,17 +132,18 @@ int update_pass_blocks_per_cu(int K, bool bf16);
 int update_pass_lds(int K, bool bf16, int lds_per_cu);
 // One-pass mean step (no penalty components): `rows` blocks of
 // fused_vectors_per_thread(K, bf16) * kFusedThreads vectors each, leaving
-// rows x (K+1) norm partials (each block's K+1 sums contiguous) and the unit marked; then one block per entry
-// of `table` turns marked units' partials into their records.
+// rows x (K+1) norm partials (each block's K+1 sums contiguous); then one
+// block per unit turns them into its record.
 int fused_vectors_per_thread(int K, bool bf16);
 // `lds`: dynamic LDS per block capping its resident blocks per CU
 // (one_pass_lds), as for the update pass.
 int one_pass_lds(int K, bool bf16, int lds_per_cu);
 hipError_t launch_fused_mean(int K, bool bf16, int rows, int lds, float* theta, float* mom,
-                             void* const* reps, double* partials, UnitRecord* rec, int64_t n,
+                             void* const* reps, double* partials, int64_t n,
                              double lr, double rho, hipStream_t stream);
-// `fold`: some unit has slices to sum first.
-hipError_t launch_fused_finish(int K, const FinishEntry* table, int units, bool fold, hipStream_t stream);
+// The records of 1 to kMaxFinishUnits units, of which the first `sliced` have
+// slices to sum first.
+hipError_t launch_fused_finish(int K, const FinishDesc* unit, int count, int sliced, hipStream_t stream);
 hipError_t launch_copy(void* dst, const void* src, int64_t nbytes, int blocks,
                        hipStream_t stream);
 // The update pass's loads and stores (whole vectors only) with no arithmetic.

@@ -923,8 +923,7 @@ __global__ __launch_bounds__(gram_threads<K>()) void small_step_kernel(SmallBatc
 // average, Nesterov and the write-back need no earlier pass: one kernel reads
 // theta, b and the K replicas once and writes theta', b' and the replicas.
 // The norms G_j and ||Delta_bar|| are still summed on the way (per-block
-// partials, reduced by fused_finish_kernel) for the step's record, and the
-// unit is marked for that reduction.  A block owns V*kFusedThreads
+// partials, reduced by fused_finish_kernel) for the step's record.  A block owns V*kFusedThreads
 // consecutive vectors; a thread loads its V vectors of every buffer before
 // computing, so V*(K+2) 16-byte loads are in flight per thread (V = 2 for
 // bf16 replicas measured best here: one vector leaves the block's closing
@@ -934,7 +933,6 @@ __global__ __launch_bounds__(kFusedThreads) void fused_mean_kernel(float* __rest
                                                                    float* __restrict__ mom,
                                                                    MutPtrs<K> reps,
                                                                    double* __restrict__ partials,
-                                                                   UnitRecord* __restrict__ rec,
                                                                    int64_t nvec, int64_t n,
                                                                    double lr, double rho) {
   constexpr int VE = Vec<BF16>::VE;
@@ -1019,17 +1017,14 @@ __global__ __launch_bounds__(kFusedThreads) void fused_mean_kernel(float* __rest
     for (int w = 1; w < kWaves; ++w) t += red[w][threadIdx.x];
     partials[static_cast<int64_t>(b) * (K + 1) + threadIdx.x] = t;
   }
-  if (b == 0 && threadIdx.x == 0) rec->finish_pending = 1;
 }
 
-// The sums over rows r0, r0 + step, ... (`count` of them) of a one-pass
-// unit's partials [rows][K+1], per column in a fixed order, in tot[K+1]
-// (shared memory).  Thread t always reads column t % NV and a wave's loads
-// are contiguous when step is 1; U loads per thread are in flight at a time,
+// The sums over `count` rows [count][K+1], per column in a fixed order, in
+// tot[K+1] (shared memory).  Thread t always reads column t % NV and a
+// wave's loads are contiguous; U loads per thread are in flight at a time,
 // and the threads' sums are added per column in thread order.
 template <int K>
-__device__ __forceinline__ void sum_rows(const double* partials, int r0, int step, int count, double* part,
-                                         double* tot) {
+__device__ __forceinline__ void sum_rows(const double* rows, int count, double* part, double* tot) {
   constexpr int NV = K + 1;
   constexpr int T = kDecideThreads / NV;  // rows read at a time
   constexpr int U = 8;
@@ -1041,7 +1036,7 @@ __device__ __forceinline__ void sum_rows(const double* partials, int r0, int ste
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int at = r + u * T;
-        v[u] = at < count ? partials[(r0 + static_cast<int64_t>(at) * step) * NV + c] : 0.0;
+        v[u] = at < count ? rows[static_cast<int64_t>(at) * NV + c] : 0.0;
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) s += v[u];
@@ -1056,36 +1051,45 @@ __device__ __forceinline__ void sum_rows(const double* partials, int r0, int ste
   }
 }
 
-// Large one-pass units: block (s, u) sums slice s of unit u's rows into the
-// slice's first row, so that the one block that makes the unit's record has
-// at most kFoldSlices rows left.  By itself that block read every row of a
+// The units of a record launch, those with slices first.
+template <int U>
+struct FinishBatch {
+  FinishDesc u[U];
+};
+
+// Large one-pass units: block (s, u) sums slice s of unit u's rows into row s
+// of its slice sums, so that the one block that makes the unit's record has
+// at most kFoldSlices rows to read.  The partial rows stay as they are.  By itself that block read every row of a
 // 28.3M-element unit (27,651 of nine sums) at the rate of one CU: 36 us for
 // a round's units, where the two launches take 8.8 and 6.8.
-template <int K>
-__global__ __launch_bounds__(kDecideThreads) void fused_fold_kernel(const FinishEntry* __restrict__ table) {
-  const FinishEntry ent = table[blockIdx.y];
-  const int r0 = blockIdx.x * ent.slice;
-  if (ent.slice < 2 || r0 >= ent.rows || !ent.rec->finish_pending) return;  // block-uniform
+template <int K, int U>
+__global__ __launch_bounds__(kDecideThreads) void fused_fold_kernel(FinishBatch<U> batch) {
+  const FinishDesc& unit = batch.u[U == 1 ? 0 : blockIdx.y];
+  const int r0 = blockIdx.x * unit.slice;
+  if (r0 >= unit.rows) return;  // block-uniform
   __shared__ double part[kDecideThreads];
   __shared__ double tot[K + 1];
-  sum_rows<K>(ent.partials, r0, 1, min(ent.slice, ent.rows - r0), part, tot);
-  if (threadIdx.x < K + 1) ent.partials[static_cast<int64_t>(r0) * (K + 1) + threadIdx.x] = tot[threadIdx.x];
+  sum_rows<K>(unit.partials + static_cast<int64_t>(r0) * (K + 1), min(unit.slice, unit.rows - r0), part, tot);
+  if (threadIdx.x < K + 1) unit.sums[blockIdx.x * (K + 1) + threadIdx.x] = tot[threadIdx.x];
 }
 
 // The records of one-pass steps: G_j and ||Delta_bar|| from each unit's
-// partials (in a fixed order), w_j = 1/K, beta = 1.  One block per unit of
-// `table`; units whose fused pass has not run since their last record are
-// skipped, so a round can take all its units' reductions in one launch after
-// its last fused pass.  Nothing is masked in this mode: a non-finite replica
-// shows up as a non-finite G_j (and in theta).
-template <int K>
-__global__ __launch_bounds__(kDecideThreads) void fused_finish_kernel(const FinishEntry* __restrict__ table) {
-  const FinishEntry ent = table[blockIdx.x];
-  UnitRecord* rec = ent.rec;
-  if (!rec->finish_pending) return;  // block-uniform
+// partial rows or slice sums (in a fixed order), w_j = 1/K, beta = 1.  One
+// block per unit, so a round can take all its units' reductions in one launch
+// after its last fused pass; only the units stepped are listed, since others
+// of the handle may be in flight on another stream.  Nothing is masked in
+// this mode: a non-finite replica shows up as a non-finite G_j (and in
+// theta).
+template <int K, int U>
+__global__ __launch_bounds__(kDecideThreads) void fused_finish_kernel(FinishBatch<U> batch) {
+  const FinishDesc& unit = batch.u[U == 1 ? 0 : blockIdx.x];
+  UnitRecord* rec = unit.rec;
   __shared__ double part[kDecideThreads];
   __shared__ double tot[K + 1];
-  sum_rows<K>(ent.partials, 0, ent.slice, (ent.rows + ent.slice - 1) / ent.slice, part, tot);
+  if (unit.slice > 1)
+    sum_rows<K>(unit.sums, (unit.rows + unit.slice - 1) / unit.slice, part, tot);
+  else
+    sum_rows<K>(unit.partials, unit.rows, part, tot);
   __syncthreads();
   if (threadIdx.x < K) {
     rec->norm[threadIdx.x] = sqrt(tot[threadIdx.x]);
@@ -1102,7 +1106,6 @@ __global__ __launch_bounds__(kDecideThreads) void fused_finish_kernel(const Fini
     rec->z_tested = 0;
     rec->stepped = 1;
     rec->round = rec->round + 1;
-    rec->finish_pending = 0;
   }
 }
 
@@ -1278,24 +1281,33 @@ constexpr int fused_v() {
 
 template <int K, bool BF16>
 hipError_t fused_mean_launch(int rows, int lds, float* theta, float* mom, void* const* reps, double* partials,
-                             UnitRecord* rec, int64_t n, double lr, double rho, hipStream_t stream) {
+                             int64_t n, double lr, double rho, hipStream_t stream) {
   MutPtrs<K> rp;
   for (int j = 0; j < K; ++j) rp.p[j] = reps[j];
   const int64_t nvec = n / Vec<BF16>::VE;
   hipLaunchKernelGGL((fused_mean_kernel<K, BF16, kNT2, fused_v<K, BF16>()>), dim3(rows), dim3(kFusedThreads),
-                     lds, stream, theta, mom, rp, partials, rec, nvec, n, lr, rho);
+                     lds, stream, theta, mom, rp, partials, nvec, n, lr, rho);
+  return hipGetLastError();
+}
+
+template <int K, int U>
+hipError_t fused_finish_launch_u(const FinishDesc* unit, int count, int sliced, hipStream_t stream) {
+  FinishBatch<U> batch{};
+  std::copy_n(unit, count, batch.u);
+  if (sliced > 0) {
+    hipLaunchKernelGGL((fused_fold_kernel<K, U>), dim3(kFoldSlices, sliced), dim3(kDecideThreads), 0, stream, batch);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((fused_finish_kernel<K, U>), dim3(count), dim3(kDecideThreads), 0, stream, batch);
   return hipGetLastError();
 }
 
 template <int K>
-hipError_t fused_finish_launch(const FinishEntry* table, int units, bool fold, hipStream_t stream) {
-  if (fold) {
-    hipLaunchKernelGGL((fused_fold_kernel<K>), dim3(kFoldSlices, units), dim3(kDecideThreads), 0, stream, table);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL((fused_finish_kernel<K>), dim3(units), dim3(kDecideThreads), 0, stream, table);
-  return hipGetLastError();
+hipError_t fused_finish_launch(const FinishDesc* unit, int count, int sliced, hipStream_t stream) {
+  if (count < 1 || count > kMaxFinishUnits || sliced < 0 || sliced > count) return hipErrorInvalidValue;
+  return count == 1 ? fused_finish_launch_u<K, 1>(unit, count, sliced, stream)
+                    : fused_finish_launch_u<K, kMaxFinishUnits>(unit, count, sliced, stream);
 }
 
 template <int K>
@@ -1320,10 +1332,10 @@ struct Launchers {
                 : pattern_probe_launch<K, false>(blocks, lds, theta, mom, reps, n, stream);
   }
   static hipError_t fused_mean(bool bf16, int rows, int lds, float* theta, float* mom, void* const* reps,
-                               double* partials, UnitRecord* rec, int64_t n, double lr, double rho,
+                               double* partials, int64_t n, double lr, double rho,
                                hipStream_t stream) {
-    return bf16 ? fused_mean_launch<K, true>(rows, lds, theta, mom, reps, partials, rec, n, lr, rho, stream)
-                : fused_mean_launch<K, false>(rows, lds, theta, mom, reps, partials, rec, n, lr, rho, stream);
+    return bf16 ? fused_mean_launch<K, true>(rows, lds, theta, mom, reps, partials, n, lr, rho, stream)
+                : fused_mean_launch<K, false>(rows, lds, theta, mom, reps, partials, n, lr, rho, stream);
   }
 };
 

@@ -46,7 +46,9 @@ struct Unit {
   int64_t n = 0;
   int rows = 1;         // Gram-pass blocks = partial rows (one-pass mode: fused blocks)
   int blocks2 = 1;      // update-pass blocks
+  int slice = 1;        // one-pass mode: rows per slice of the fold launch (1: none)
   double* partials = nullptr;
+  double* sums = nullptr;  // one-pass mode: slice sums of a sliced unit
   UnitRecord* rec = nullptr;
   hipEvent_t done = nullptr;
   hipEvent_t prof[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -124,7 +126,6 @@ struct edit_outer {
   int32_t profile_every = 0;  // record kernel events on units l with l % every == 0
   char* arena = nullptr;   // one device allocation for every unit's scratch
   void* noalloc = nullptr; // this device's fixed scratch array (step_layer_noalloc)
-  FinishEntry* finish_table = nullptr;  // one-pass mode: [L] entries, in the arena
   bool one_pass = false;
   Offload off;
   std::vector<Unit> units;
@@ -336,7 +337,7 @@ edit_status_t edit_outer_init(const edit_outer_config_t* cfg, edit_outer_t* out)
   const size_t rec_bytes = (sizeof(UnitRecord) + 255) & ~size_t(255);
   size_t total = 0;
   h->units.resize(cfg->num_layers);
-  std::vector<size_t> offs(cfg->num_layers);
+  std::vector<size_t> offs(cfg->num_layers), sums_offs(cfg->num_layers);
   for (int l = 0; l < cfg->num_layers; ++l) {
     Unit& u = h->units[l];
     u.n = h->numel[l];
@@ -358,9 +359,12 @@ edit_status_t edit_outer_init(const edit_outer_config_t* cfg, edit_outer_t* out)
     const size_t per_row = h->one_pass ? size_t(K + 1) : size_t(num_pairs(K));
     const size_t part_bytes = (per_row * u.rows * sizeof(double) + 255) & ~size_t(255);
     total += rec_bytes + part_bytes;
+    if (h->one_pass) u.slice = fold_slice(u.rows, K);
+    if (u.slice > 1) {
+      sums_offs[l] = total;
+      total += (per_row * kFoldSlices * sizeof(double) + 255) & ~size_t(255);
+    }
   }
-  const size_t table_off = total;
-  if (h->one_pass) total += (sizeof(FinishEntry) * cfg->num_layers + 255) & ~size_t(255);
   e = hipMalloc(reinterpret_cast<void**>(&h->arena), total);
   if (e != hipSuccess) {
     delete h;
@@ -371,15 +375,8 @@ edit_status_t edit_outer_init(const edit_outer_config_t* cfg, edit_outer_t* out)
     Unit& u = h->units[l];
     u.rec = reinterpret_cast<UnitRecord*>(h->arena + offs[l]);
     u.partials = reinterpret_cast<double*>(h->arena + offs[l] + rec_bytes);
+    if (u.slice > 1) u.sums = reinterpret_cast<double*>(h->arena + sums_offs[l]);
     e = hipEventCreateWithFlags(&u.done, hipEventDisableTiming);
-  }
-  if (e == hipSuccess && h->one_pass) {
-    std::vector<FinishEntry> table(cfg->num_layers);
-    for (int l = 0; l < cfg->num_layers; ++l)
-      table[l] = {h->units[l].partials, h->units[l].rec, h->units[l].rows, fold_slice(h->units[l].rows, K)};
-    h->finish_table = reinterpret_cast<FinishEntry*>(h->arena + table_off);
-    e = hipMemcpy(h->finish_table, table.data(), sizeof(FinishEntry) * table.size(),
-                  hipMemcpyHostToDevice);
   }
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
@@ -565,20 +562,28 @@ struct Enqueue {
     hipError_t e = launch_decide_gram(K, gram, u.rec, prm, s);
     return e == hipSuccess ? EDIT_OK : fail_hip(e, "decide launch");
   }
-  // one-pass mode: the fused pass of `layer`, and the record reduction of
-  // `units` table entries from `first` (marked units only)
+  // one-pass mode: the fused pass of `layer`, and the record reductions of
+  // the units stepped
   edit_status_t fused(int32_t layer, float* theta, float* momentum, void* const* replicas) {
     Unit& u = h->units[layer];
     void* const* mreps = u.n == 0 ? kNoReplicas : replicas;
-    hipError_t e = launch_fused_mean(K, bf16, u.rows, h->fused_lds, theta, momentum, mreps, u.partials, u.rec, u.n,
+    hipError_t e = launch_fused_mean(K, bf16, u.rows, h->fused_lds, theta, momentum, mreps, u.partials, u.n,
                                      h->cfg.outer_lr, h->cfg.momentum, s);
     return e == hipSuccess ? EDIT_OK : fail_hip(e, "one-pass launch");
   }
-  edit_status_t records(int32_t first, int32_t units) {
-    bool fold = false;
-    for (int32_t l = first; l < first + units; ++l) fold = fold || fold_slice(h->units[l].rows, K) > 1;
-    hipError_t e = launch_fused_finish(K, h->finish_table + first, units, fold, s);
-    return e == hipSuccess ? EDIT_OK : fail_hip(e, "record launch");
+  edit_status_t records(const int32_t* layers, int32_t count) {
+    for (int32_t at = 0; at < count; at += kMaxFinishUnits) {
+      const int units = std::min<int32_t>(count - at, kMaxFinishUnits);
+      FinishDesc d[kMaxFinishUnits];
+      int sliced = 0, rest = units;  // sliced units from the front, others from the back
+      for (int i = 0; i < units; ++i) {
+        const Unit& u = h->units[layers[at + i]];
+        d[u.slice > 1 ? sliced++ : --rest] = {u.partials, u.sums, u.rec, u.rows, u.slice};
+      }
+      hipError_t e = launch_fused_finish(K, d, units, sliced, s);
+      if (e != hipSuccess) return fail_hip(e, "record launch");
+    }
+    return EDIT_OK;
   }
   edit_status_t finish(int32_t layer) {
     Unit& u = h->units[layer];
@@ -649,7 +654,7 @@ edit_status_t edit_outer_step_layer(edit_outer_t h, int32_t layer, float* theta,
     EDIT_TRY(q.fused(layer, theta, momentum, replicas));
     EDIT_TRY(q.event(h->units[layer], layer, 1));
     EDIT_TRY(q.event(h->units[layer], layer, 2));
-    EDIT_TRY(q.records(layer, 1));
+    EDIT_TRY(q.records(&layer, 1));
     EDIT_TRY(q.event(h->units[layer], layer, 3));
     return q.finish(layer);
   }
@@ -753,7 +758,7 @@ edit_status_t edit_outer_step_round(edit_outer_t h, int32_t count, const int32_t
       EDIT_TRY(q.event(h->units[l], l, 2));
       EDIT_TRY(q.event(h->units[l], l, 3));
     }
-    EDIT_TRY(q.records(0, h->cfg.num_layers));
+    EDIT_TRY(q.records(layers, count));
     return q.finish_round(layers, count);
   }
   // Consecutive units go in batches of three launches: Gram pass, decisions,
@@ -913,7 +918,7 @@ edit_status_t edit_outer_step_round_host(edit_outer_t h, int32_t count, const in
       EDIT_TRY(q.fused(l, dth, db, reps));
       EDIT_TRY(q.event(u, l, 1));
       EDIT_TRY(q.event(u, l, 2));
-      EDIT_TRY(q.records(l, 1));
+      EDIT_TRY(q.records(&l, 1));
       EDIT_TRY(q.event(u, l, 3));
     } else {
       EDIT_TRY(q.step_unit(l, q.desc(l, dth, db, reps)));

@@ -92,6 +92,72 @@ def test_one_pass_round_matches_unit_by_unit(K, dtype):
         assert x.round == y.round == 3
 
 
+def _random_units(cfg, seed):
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    units = []
+    for n in cfg.layer_numel:
+        th = torch.empty(n, device=DEV).normal_(0.0, 0.02, generator=gen)
+        reps = [(th + (j + 1) * 1e-3 * torch.empty(n, device=DEV).normal_(0.0, 1.0, generator=gen))
+                .to(cfg.torch_dtype) for j in range(cfg.num_workers)]
+        units.append((th, torch.zeros_like(th), reps))
+    return units
+
+
+def _same_units(ua, a, ub, b):
+    for x, y in zip(ua, ub):
+        assert torch.equal(x[0], y[0]) and torch.equal(x[1], y[1])
+        assert all(torch.equal(p, q) for p, q in zip(x[2], y[2]))
+    for u in range(len(ua)):
+        x, y = a.state_get(u), b.state_get(u)
+        assert np.array_equal(x.norm, y.norm) and x.synced_norm == y.synced_norm and x.round == y.round, f"unit {u}"
+
+
+# rows of partials at K = 32, bf16 (512 elements each): past 3,971 rows a
+# unit's rows are summed in slices
+_SLICED, _WHOLE = 512 * 4500 + 5, 512 * 3971
+
+
+def test_one_pass_rounds_on_two_streams_leave_each_other_alone():
+    """Units of one handle may run on different streams: a round makes the
+    records of its own units and neither reads nor writes the partial rows of
+    a unit that another stream has in flight.  Rounds over disjoint units on
+    two streams give the bits and records of the same rounds one by one."""
+    cfg = OuterConfig(32, [_SLICED, _SLICED, _WHOLE, _SLICED, 700, _SLICED], "bf16", flags=ONE_PASS)
+    parts = [[0, 2, 3], [5, 4, 1]]
+    one = _random_units(cfg, 3)
+    two = [(t.clone(), b.clone(), [r.clone() for r in reps]) for t, b, reps in one]
+    streams = [torch.cuda.Stream(DEV) for _ in parts]
+    with EditOuter(cfg, DEV) as a, EditOuter(cfg, DEV) as b:
+        plans = [b.prepare_round([two[u] for u in p], layers=p) for p in parts]
+        torch.cuda.synchronize()
+        for _ in range(6):
+            for p in parts:
+                a.step_round([one[u] for u in p], layers=p)
+            for plan, s in zip(plans, streams):
+                plan.run(stream=s)
+        torch.cuda.synchronize()
+        _same_units(one, a, two, b)
+
+
+@pytest.mark.parametrize("count", [64, 65, 130])
+def test_one_pass_round_of_many_units(count):
+    """Records are made 64 units to a launch, sliced units first among them."""
+    sizes = [5 + u for u in range(count)]
+    for u in (0, 63, count - 1):
+        sizes[u] = _SLICED
+    cfg = OuterConfig(32, sizes, "bf16", flags=ONE_PASS)
+    order = list(range(count))[::-1]
+    one = _random_units(cfg, count)
+    two = [(t.clone(), b.clone(), [r.clone() for r in reps]) for t, b, reps in one]
+    with EditOuter(cfg, DEV) as a, EditOuter(cfg, DEV) as b:
+        for _ in range(2):
+            for u in order:
+                a.step_layer(u, *one[u])
+            b.step_round([two[u] for u in order], layers=order)
+        torch.cuda.synchronize()
+        _same_units(one, a, two, b)
+
+
 def test_one_pass_nonfinite_is_reported_not_masked():
     """There is no norm before the average in this mode: a NaN in a replica
     reaches theta at that element, and the worker's reported G_j is NaN."""
