@@ -18,6 +18,7 @@
 #include <string>
 #include <vector>
 
+#include "disjoint_ranges.h"
 #include "edit_outer_internal.h"
 #include "edit_group_internal.h"
 
@@ -768,38 +769,76 @@ edit_status_t edit_outer_step_round(edit_outer_t h, int32_t count, const int32_t
   // batch: nine 2.9M units (K = 4 fp32) 374 and 329 us, six 4.2M (K = 8
   // bf16) 364 and 293, six 12.8M fp32 (K = 8) 1,513 and 1,428.  Units of one
   // Gram block take no part in that: they are stepped whole, a block each,
-  // in launches of their own (units are independent, so only the launch that
-  // runs them changes).  In a batch with a large unit they would wait for its
-  // passes (a 51.4M unit and two gains at K = 16: 1,100 us against 1,050).
+  // in launches of their own.  In a batch with a large unit they would wait
+  // for its passes (a 51.4M unit and two gains at K = 16: 1,100 us against
+  // 1,050).  Units that wait for their launch share no buffer: a unit that
+  // shares one with a waiting unit (a tied parameter listed twice) first sends
+  // off all that wait, so that the units of a launch are independent and
+  // shared buffers see the steps in the round's order.
   const int most = batch_units(K);
   UnitDesc batch[kMaxBatchUnits], small[kMaxBatchUnits];
   int in = 0, nsmall = 0;
   int64_t bytes = 0;  // read by the batch's Gram pass
+  // at most 2 * 16 units of 18 buffers up to K = 16, 2 * 8 of 34 above
+  DisjointRanges<kMaxBatchUnits * (EDIT_MAX_K + 4)> waiting;
+  ByteRange r[EDIT_MAX_K + 2];
+  auto ranges = [&](const UnitDesc& d) {  // the unit's buffers in r; their number
+    if (d.n == 0) return 0;
+    auto range = [&](const void* p, int64_t each) {
+      const uintptr_t lo = reinterpret_cast<uintptr_t>(p);
+      return ByteRange{lo, lo + static_cast<uintptr_t>(d.n * each)};
+    };
+    r[0] = range(d.theta, 4);
+    r[1] = range(d.mom, 4);
+    for (int j = 0; j < K; ++j) r[2 + j] = range(d.reps[j], q.bf16 ? 2 : 4);
+    return K + 2;
+  };
   auto flush = [&]() -> edit_status_t {
     if (in == 0) return EDIT_OK;
     q.cache_end(batch, in);
     const int units = in;
     in = 0;
     bytes = 0;
+    waiting.clear();
+    for (int i = 0; i < nsmall; ++i) {
+      const int nr = ranges(small[i]);
+      waiting.add(r, nr);
+    }
     return q.step(batch, units);
   };
   auto flush_small = [&]() -> edit_status_t {
+    if (nsmall == 0) return EDIT_OK;
     const int units = nsmall;
     nsmall = 0;
-    return units > 0 ? q.step(small, units) : EDIT_OK;
+    waiting.clear();
+    for (int i = 0; i < in; ++i) {
+      const int nr = ranges(batch[i]);
+      waiting.add(r, nr);
+    }
+    return q.step(small, units);
   };
   for (int32_t i = 0; i < count; ++i) {
     const int32_t l = layers[i];
     const UnitDesc d = q.desc(l, theta[i], momentum[i], replicas + static_cast<size_t>(i) * K);
-    if (q.profiled(l)) {
+    const bool alone = q.profiled(l);
+    const bool whole = !alone && d.rows == 1;
+    const int64_t b = q.gram_bytes(l);
+    if (alone || (!whole && (in == most || (in > 0 && bytes + b > kBatchBytes)))) EDIT_TRY(flush());
+    if (whole && nsmall == most) EDIT_TRY(flush_small());
+    int nr = ranges(d);
+    if (waiting.meets(r, nr)) {
       EDIT_TRY(flush());
+      EDIT_TRY(flush_small());
+      nr = ranges(d);  // the flushes used r
+    }
+    if (alone) {
       EDIT_TRY(q.step_unit(l, d));
-    } else if (d.rows == 1) {
+      continue;
+    }
+    waiting.add(r, nr);
+    if (whole) {
       small[nsmall++] = d;
-      if (nsmall == most) EDIT_TRY(flush_small());
     } else {
-      const int64_t b = q.gram_bytes(l);
-      if (in == most || (in > 0 && bytes + b > kBatchBytes)) EDIT_TRY(flush());
       batch[in++] = d;
       bytes += b;
     }

@@ -6,7 +6,9 @@ of a unit do not depend on the batch, so every schedule must give the bits of
 unit-by-unit edit_outer_step_layer calls.  The Gram pass reads the end of its
 input through the cache and the rest non-temporally, two loops of the same
 sums, so a step over a unit that crosses that line must give the bits of the
-Gram and apply calls, which stream all of it.
+Gram and apply calls, which stream all of it.  Units of a round that share a
+buffer are no longer independent; a round then has to give the bits of the
+calls in its order.
 """
 import numpy as np
 import pytest
@@ -78,6 +80,48 @@ def test_round_in_batches_matches_unit_by_unit(mix, K, dtype):
         torch.cuda.synchronize()
         _same(one, all_, f"{mix} K={K} {dtype}")
         _same_state(a, b, len(sizes), f"{mix} K={K} {dtype}")
+
+
+# (unit, buffer) that is a piece of (another unit, buffer) from the given
+# vector on; buffers: 0 theta, 1 momentum, 2.. replicas.  Sizes in vectors.
+_TIES = {
+    "large with large": ([600, 700, 600, 500], [(2, b, 0, b, 0) for b in range(3)]),
+    "piece of the one before": ([5000, 4000, 3000, 300], [(1, 3, 0, 3, 1000), (2, 0, 1, 0, 7), (3, 1, 2, 1, 2700)]),
+    "small with large": ([900, 100, 256, 800, 400], [(1, 0, 0, 0, 800), (2, 3, 3, 3, 100), (1, 1, 4, 1, 7)]),
+    "small with small": ([200, 150, 256, 1, 40], [(1, 1, 0, 1, 50), (1, 2, 2, 2, 90), (4, 0, 2, 0, 216)]),
+    "past a full batch": ([300 + u for u in range(18)] + [20 + u for u in range(20)],
+                          [(16, 1, 17, 1, 1), (1, 2, 16, 2, 3), (19, 0, 37, 0, 5), (36, 3, 2, 3, 10)]),
+}
+
+
+@pytest.mark.parametrize("every", [0, 3])
+@pytest.mark.parametrize("K,dtype", [(4, "f32"), (8, "bf16"), (16, "bf16"), (17, "f32")])
+@pytest.mark.parametrize("ties", list(_TIES))
+def test_round_with_shared_buffers_matches_unit_by_unit(ties, K, dtype, every):
+    """Also with kernel timing on every third unit, whose launches go ahead of
+    the units that wait."""
+    ve = 8 if dtype == "bf16" else 4
+    vecs, shared = _TIES[ties]
+    sizes = [v * ve for v in vecs]
+    cfg = OuterConfig(K, sizes, dtype, clip_threshold=0.05)
+
+    def units():
+        made = [[t, b, *reps] for t, b, reps in _inputs(cfg, torch.Generator(device=DEV).manual_seed(K))]
+        for u, buf, of, of_buf, at in shared:
+            made[u][buf] = made[of][of_buf][at * ve:at * ve + sizes[u]]
+            assert made[u][buf].numel() == sizes[u]
+        return [(m[0], m[1], m[2:]) for m in made]
+
+    one, all_ = units(), units()
+    with EditOuter(cfg, DEV) as a, EditOuter(cfg, DEV) as b:
+        b.set_profiling(every)
+        for _ in range(2):
+            for u, unit in enumerate(one):
+                a.step_layer(u, *unit)
+            b.step_round(all_)
+        torch.cuda.synchronize()
+        _same(one, all_, f"{ties} K={K} {dtype}")
+        _same_state(a, b, len(sizes), f"{ties} K={K} {dtype}")
 
 
 @pytest.mark.parametrize("K,dtype,n", [(8, "bf16", 12_000_005), (4, "f32", 9_000_003), (2, "bf16", 25_000_001),
