@@ -285,19 +285,22 @@ constexpr int kDecideThreads = 1024;  // one block; wide so the partial loads ov
 
 // Reduce a unit's partial rows [rows][NP] in a fixed order into gram[NP]
 // (shared memory).  Thread t reads the flat array at t, t + S, t + 2S, ...
-// with S the largest multiple of NP within the block, so it always reads
+// with S a multiple of NP within the block, so it always reads
 // column t % NP and a wave's loads are contiguous; the S threads' sums are
-// then added per column in thread order.  The rows were just written by
-// every XCD's blocks, so the loads come from the Infinity Cache or HBM and
-// the reduction is latency-bound: all of a thread's loads for 256 rows are
-// in flight at once up to K = 16, 48 at a time above.  As [NP][rows], whose
-// loads touched a cache line per lane, over up to 1,023 rows the decision
-// kernel took 9.2 us at K = 4 (1.05M fp32 elements; now 4.4), 6.8 at K = 8
+// then added per column in thread order, by one thread per column, so at
+// most 32 threads share a column: with as many as fit the block, K = 1 and 2
+// added 1,023 and 340 terms one after the other (a step of 65,536 fp32
+// elements at K = 1 29.0 us, of 300,000 at K = 2 21.2; now 17.0 and 16.0).
+// The rows were just written by every XCD's blocks, so the loads come from
+// the Infinity Cache or HBM and the reduction is latency-bound: all of a
+// thread's loads for 256 rows are in flight at once up to K = 16, 48 at a
+// time above.  As [NP][rows], whose loads touched a cache line per lane, over
+// up to 1,023 rows the decision kernel took 9.2 us at K = 4 (1.05M fp32 elements; now 4.4), 6.8 at K = 8
 // (4.7) and 79 at K = 32 (27, bound by one CU reading 1.1 MB).
 template <int K>
 __device__ void reduce_partials(const double* partials, int rows, double* gram, double* scratch) {
   constexpr int NP = K * (K + 1) / 2;
-  constexpr int T = kDecideThreads / NP;
+  constexpr int T = kDecideThreads / NP < 32 ? kDecideThreads / NP : 32;  // threads per column
   constexpr int S = NP * T;
   constexpr int kAll = (256 + T - 1) / T;
   constexpr int U = kAll < 48 ? kAll : 48;
