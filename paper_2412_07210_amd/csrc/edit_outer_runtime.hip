@@ -461,6 +461,17 @@ DecideParams decide_params(const edit_outer* h) {
 // it another unit in the batch saves nothing (rounds of six 1B units, 1.03 GB
 // each: 3,394 us at one unit per batch and at four, 3,411 at six).
 constexpr int64_t kBatchBytes = int64_t(4) << 30;
+// From 9 to 16 workers a unit that reads more than this takes a batch of its
+// own.  That Gram pass reads all of its input through the cache, and the
+// update pass finds the end of it there; a larger batch loses that for all
+// its units but the last.  Rounds of four units, us at one and at four per
+// batch: bf16 of 128 MB each 359 and 336 (K = 16), 338 and 323 (K = 12); of
+// 256 MB 633 and 633, 613 and 610, K = 9 706 and 717; of 448 MB 1,073 and
+// 1,082, 1,016 and 1,040, K = 9 1,202 and 1,219.  fp32 at K = 16 of 448 MB 962
+// and 960, of 1 GB 2,169 and 2,186.  Above K = 16 the decision costs more than
+// that: K = 24 bf16 of 448 MB 1,225 and 1,208, K = 32 of 1 GB 2,992 and 2,943.
+constexpr int64_t kAloneBytesBf16 = int64_t(240) << 20;
+constexpr int64_t kAloneBytesF32 = int64_t(768) << 20;
 // The end of a step's Gram input that is read through the cache (VALU pass),
 // for the update pass to find in the 256 MB Infinity Cache, which also takes
 // that pass's stores.  Six 1B bf16 units: 3,412 us with none, 3,405 at 120
@@ -492,7 +503,12 @@ struct Enqueue {
   }
   // bytes of theta and the replicas per element, which the Gram pass reads
   int64_t element_bytes() const { return 4 + (bf16 ? 2 : 4) * static_cast<int64_t>(K); }
-  int64_t gram_bytes(int32_t layer) const { return h->units[layer].n * element_bytes(); }
+  // What a unit takes of a batch's kBatchBytes.
+  int64_t batch_bytes(int32_t layer) const {
+    const int64_t b = h->units[layer].n * element_bytes();
+    const bool alone = K > 8 && K <= 16 && b > (bf16 ? kAloneBytesBf16 : kAloneBytesF32);
+    return alone ? std::max(b, kBatchBytes) : b;
+  }
   UnitDesc desc(int32_t layer, const float* theta, float* momentum, void* const* replicas) const {
     const Unit& u = h->units[layer];
     UnitDesc d;
@@ -778,7 +794,7 @@ edit_status_t edit_outer_step_round(edit_outer_t h, int32_t count, const int32_t
   const int most = batch_units(K);
   UnitDesc batch[kMaxBatchUnits], small[kMaxBatchUnits];
   int in = 0, nsmall = 0;
-  int64_t bytes = 0;  // read by the batch's Gram pass
+  int64_t bytes = 0;  // what the batch's units take of kBatchBytes
   // at most 2 * 16 units of 18 buffers up to K = 16, 2 * 8 of 34 above
   DisjointRanges<kMaxBatchUnits * (EDIT_MAX_K + 4)> waiting;
   ByteRange r[EDIT_MAX_K + 2];
@@ -822,7 +838,7 @@ edit_status_t edit_outer_step_round(edit_outer_t h, int32_t count, const int32_t
     const UnitDesc d = q.desc(l, theta[i], momentum[i], replicas + static_cast<size_t>(i) * K);
     const bool alone = q.profiled(l);
     const bool whole = !alone && d.rows == 1;
-    const int64_t b = q.gram_bytes(l);
+    const int64_t b = q.batch_bytes(l);
     if (alone || (!whole && (in == most || (in > 0 && bytes + b > kBatchBytes)))) EDIT_TRY(flush());
     if (whole && nsmall == most) EDIT_TRY(flush_small());
     int nr = ranges(d);

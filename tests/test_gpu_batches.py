@@ -82,6 +82,32 @@ def test_round_in_batches_matches_unit_by_unit(mix, K, dtype):
         _same_state(a, b, len(sizes), f"{mix} K={K} {dtype}")
 
 
+@pytest.mark.parametrize("K,dtype,sizes", [
+    # a batch's last 160 MB of Gram input are read through the cache: the line
+    # falls into the first of three units, the second of four, between two
+    (8, "bf16", [12_000_005, 3_000_000, 1_000_003]),
+    (4, "f32", [3_000_001, 4_000_002, 2_500_000, 3_500_003]),
+    (1, "f32", [6_000_000, 10_000_000, 10_000_000]),
+    # the third unit would take the batch past 4 GiB
+    (2, "bf16", [200_000_001, 200_000_002, 200_000_003]),
+    # units that take a batch of their own (over 240 MiB bf16, 768 MiB fp32),
+    # first, between and behind others
+    (12, "bf16", [9_000_001, 1_000_000, 700_001, 9_000_002, 9_000_003, 3]),
+    (16, "f32", [400_000, 12_000_001, 300_001]),
+])
+def test_round_across_the_byte_limits_matches_unit_by_unit(K, dtype, sizes):
+    cfg = OuterConfig(K, sizes, dtype, clip_threshold=0.05)
+    one = _inputs(cfg, torch.Generator(device=DEV).manual_seed(K))
+    all_ = _copy(one)
+    with EditOuter(cfg, DEV) as a, EditOuter(cfg, DEV) as b:
+        for u, unit in enumerate(one):
+            a.step_layer(u, *unit)
+        b.step_round(all_)
+        torch.cuda.synchronize()
+        _same(one, all_, f"K={K} {dtype}")
+        _same_state(a, b, len(sizes), f"K={K} {dtype}")
+
+
 # (unit, buffer) that is a piece of (another unit, buffer) from the given
 # vector on; buffers: 0 theta, 1 momentum, 2.. replicas.  Sizes in vectors.
 _TIES = {
