@@ -372,8 +372,8 @@ __device__ __forceinline__ void gnesterov(double dhat, float th, float b, double
 // taken from the unit's end so the first ones find what group_dbar read last.
 // The launch reserves dynamic LDS so that four 128-thread blocks at most run
 // on a CU (kGroupUpdateBlocks): 324 -> 316 us per step of a 51.4M bf16 unit
-// (with everything non-temporal 350 uncapped, 345 at four, 351 at six;
-// one-wave blocks 346 at six or eight, 256-thread blocks 347 at two or three).
+// (with everything non-temporal 350 uncapped, 345 at four, 351 at five;
+// one-wave blocks 346 at five or eight, 256-thread blocks 347 at two).
 template <bool BF16, bool NT>
 __global__ __launch_bounds__(kGroupUpdateThreads) void group_update_kernel(
     const GroupRecord* __restrict__ rec, const float* __restrict__ dbar, float* __restrict__ theta,

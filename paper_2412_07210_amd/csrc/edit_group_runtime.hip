@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "edit_group_internal.h"
+#include "lds_cap.h"
 
 using namespace edit;
 
@@ -183,7 +184,7 @@ edit_status_t edit_group_init(const edit_outer_config_t* cfg, int32_t rank, edit
   h->cfg.layer_numel = h->numel.data();
   h->rank = rank;
   h->device = dev;
-  h->update_lds = (lds_per_cu / kGroupUpdateBlocks) & ~255;
+  h->update_lds = lds_for_blocks(kGroupUpdateBlocks, 0, lds_per_cu);
   const bool bf16 = cfg->replica_dtype == EDIT_BF16;
   const int ve = bf16 ? 8 : 4;
   const int cap_dbar = num_cu * group_dbar_blocks_per_cu();

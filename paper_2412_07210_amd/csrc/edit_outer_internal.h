@@ -126,9 +126,8 @@ hipError_t launch_decide_gram(int K, const double* gram, UnitRecord* rec, const 
 // cap its resident blocks per CU (update_pass_lds).
 hipError_t launch_update(int K, bool bf16, const UnitDesc* unit, int count, int lds, double lr, double rho,
                          hipStream_t stream);
-// Update-pass blocks resident per CU, and the dynamic LDS per block that
-// caps them there given the CU's LDS bytes.
-int update_pass_blocks_per_cu(int K, bool bf16);
+// The dynamic LDS per block that caps the update pass's resident blocks, given
+// the CU's LDS bytes.
 int update_pass_lds(int K, bool bf16, int lds_per_cu);
 // One-pass mean step (no penalty components): `rows` blocks of
 // fused_vectors_per_thread(K, bf16) * kFusedThreads vectors each, leaving

@@ -762,7 +762,7 @@ __device__ __forceinline__ void update_vector(float* theta, float* mom, const Mu
 // vectors (a flat grid): the hardware dispatcher then keeps the in-flight
 // window of each of the 2K+4 streams short and ordered (measured 5.5 TB/s
 // here against 4.9 TB/s for a persistent grid-stride loop).  The launch
-// reserves dynamic LDS so that six blocks at most run on a CU
+// reserves dynamic LDS so that few blocks at a time run on a CU
 // (update_pass_blocks_per_cu): fewer waves in flight serve this traffic
 // faster.  Blocks are taken from the unit's end; forward order measured the
 // same.
