@@ -42,7 +42,7 @@ def log(msg: str) -> None:
 
 def kernel_code_hash(text: str) -> str:
     """Hash of kernel source with comments and whitespace removed: the identity
-    of the code the HBM counters were taken on (a comment edit keeps it)."""
+    of the code the traffic counters were taken on (a comment edit keeps it)."""
     import re
     text = re.sub(r"/\*.*?\*/", " ", text, flags=re.S)
     text = re.sub(r"//[^\n]*", " ", text)
@@ -79,9 +79,10 @@ def unit_bytes(n: int, K: int, R: int, active: int, rolled_back: bool, one_pass:
 
 
 def measured_traffic(kernel: str, workload: str):
-    """HBM bytes per launch of `kernel` (pass2, fused) from committed rocprofv3
-    counters, if they were taken on this workload and on the current kernel
-    code; else None."""
+    """Bytes per launch that `kernel` (pass2, fused) moves between the L2s and
+    memory, from committed rocprofv3 counters, if they were taken on this
+    workload and on the current kernel code; else None.  The counters sit in
+    front of the Infinity Cache, so its hits are among the bytes."""
     try:
         with open(COUNTERS_FILE) as f:
             data = json.load(f)
@@ -96,7 +97,7 @@ def measured_traffic(kernel: str, workload: str):
 
 
 def _on_traffic(traffic, avg_ms):
-    """GB/s of the counter-measured HBM bytes per launch over the event average."""
+    """GB/s of the counter-measured bytes per launch over the event average."""
     return None if traffic is None else round(traffic / (avg_ms * 1e-3) / 1e9, 2)
 
 
@@ -530,7 +531,7 @@ def summarize_profiles(out_dir: str, bench_json: str, variant: str = "two-pass")
     with open(os.path.join(prof_dir, f"{name}_kernel_trace_stats.md"), "w") as f:
         f.write("\n".join(lines) + "\n")
 
-    # HBM counters, calibrated on the 2 GiB copy probe of the same run
+    # traffic counters, calibrated on the 2 GiB copy probe of the same run
     def counters(which):
         with open(os.path.join(out_dir, f"prof_{which}{sfx}", f"{tag}_counter_collection.csv")) as f:
             rows = sorted((int(r["Dispatch_Id"]), _kernel_kind(r["Kernel_Name"]), int(r["Grid_Size"]),
@@ -558,7 +559,9 @@ def summarize_profiles(out_dir: str, bench_json: str, variant: str = "two-pass")
                 f"{variant}_fetch_scale": round(fetch_scale, 4),
                 f"{variant}_write_scale": round(write_scale, 4),
                 f"{variant}_commands": [cmds["fetch"], cmds["write"]]})
-    lines = [f"# HBM traffic counters: 1B K=8 {title}", "",
+    lines = [f"# Traffic counters: 1B K=8 {title}", "",
+             "Bytes between the L2s and memory: the counters sit in front of the Infinity Cache, so what it "
+             "serves is counted as well as what HBM does.", "",
              "Commands (from the repository root; `<out>` = the directory the profiler wrote to):", "",
              "    " + cmds["fetch"], "    " + cmds["write"], "",
              f"Calibration on the plain 2 GiB copy kernel in the same runs: FETCH_SIZE reads "
@@ -1084,6 +1087,7 @@ def main(argv=None) -> int:
             "unit": "GB/s",
             "frac": round(achieved / PEAK_HBM_GBPS, 4),
             "traffic": measured_traffic("fused", wl.name),
+            "traffic_scope": "between the L2s and memory (Infinity Cache and HBM)",
             "achieved_on_traffic": _on_traffic(measured_traffic("fused", wl.name), avg_ms),
             "bytes_per_launch": int(per_launch),
             "avg_launch_ms": round(avg_ms, 5),
@@ -1104,6 +1108,7 @@ def main(argv=None) -> int:
             "unit": "GB/s",
             "frac": round(achieved / PEAK_HBM_GBPS, 4),
             "traffic": traffic,
+            "traffic_scope": "between the L2s and memory (Infinity Cache and HBM)",
             "achieved_on_traffic": _on_traffic(traffic, avg_ms),
             "bytes_per_launch": int(per_launch),
             "avg_launch_ms": round(avg_ms, 5),

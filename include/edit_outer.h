@@ -148,7 +148,9 @@ int64_t edit_outer_min_warmup(double alpha, double delta);
 /* One outer step of unit `layer` (Sec. 3.2, Algorithm 2), enqueued on
  * `stream` (a hipStream_t; NULL = the default stream).  No host
  * synchronisation; the norm/Gram pass, the one-block decision kernel and the
- * update pass run in stream order.
+ * update pass run in stream order.  A unit of at most 256 16-byte vectors
+ * (2,048 bf16 or 1,024 fp32 elements) takes all three in one launch of one
+ * block.
  *   theta    [n] fp32, in: theta_t, out: theta_{t+1} (unchanged on rollback)
  *   momentum [n] fp32, in/out: outer momentum b (zero-initialised by caller)
  *   replicas host array of K device pointers, each [n] of replica_dtype;
@@ -166,11 +168,12 @@ edit_status_t edit_outer_step_layer(edit_outer_t h, int32_t layer, float *theta,
  * in that order.  Consecutive units are stepped in batches of up to 16 (8
  * above K = 16), each batch with one Gram launch, one launch of its units'
  * one-block decisions and one update launch; the partial sums of a unit do
- * not depend on its batch.  A unit of at most 256 16-byte vectors (2,048
- * bf16 or 1,024 fp32 elements) is stepped whole by one block of a small
- * launch that carries up to as many such units, after the batches before
- * it.  Units that kernel timing (edit_outer_set_profiling) covers keep
- * launches of their own.
+ * not depend on its batch.  Units of at most 256 16-byte vectors, which one
+ * block steps whole, are gathered over the round into launches of up to as
+ * many, before or after the batches around them.  Units that kernel timing
+ * (edit_outer_set_profiling) covers keep launches of their own.  Units may
+ * share buffers with each other (tied parameters); those are stepped in the
+ * given order.
  *   layers   [count] unit indices, each at most once (else EDIT_EINVAL)
  *   theta    [count] device pointers, as in edit_outer_step_layer
  *   momentum [count] device pointers
@@ -196,8 +199,10 @@ edit_status_t edit_outer_step_round(edit_outer_t h, int32_t count, const int32_t
  *   replicas      [count * K] device pointers, as in edit_outer_step_round
  * Everything is enqueued behind `stream`'s earlier work, and `stream` waits
  * for the last copy back: after synchronising `stream` the host arrays hold
- * theta_{t+1} and b'.  The caller must not touch them before that.  Rounds on
- * one handle must be issued from one stream. */
+ * theta_{t+1} and b'.  The caller must not touch them before that, and the
+ * host arrays of different units must not overlap: a unit is copied in before
+ * the one before it has been copied back.  Rounds on one handle must be
+ * issued from one stream. */
 edit_status_t edit_outer_step_round_host(edit_outer_t h, int32_t count, const int32_t *layers,
                                          float *const *theta_host, float *const *momentum_host,
                                          void *const *replicas, void *stream);
@@ -279,11 +284,12 @@ const char *edit_outer_last_error(void);
  * whose count grows with the unit up to one block per CU (256 on MI355X),
  * so only K = 32 units of more than 63,488 16-byte vectors
  * (507,904 bf16 or 253,952 fp32 elements) are refused there.
- * All calls on one GPU share that GPU's array, which keeps the last call's
- * partials (nothing in it needs clearing: a call writes every partial it
- * reads).  Calls on one GPU must therefore not overlap: order them on one
+ * All calls on one GPU share that GPU's array (nothing in it needs clearing:
+ * a call writes every partial it reads; a unit that one block steps whole
+ * leaves it alone).  Calls on one GPU must therefore not overlap: order them on one
  * stream or with events, also across handles and host threads; overlapping
- * calls race.  The call enqueues up to three kernels and one event record and
+ * calls race.  The call enqueues three kernels, or one for a unit that one
+ * block steps whole, and one event record, and
  * makes no synchronising call, so it can be captured into a HIP graph and
  * replayed; after a replay, once the caller has synchronised,
  * edit_outer_state_get reports that replay's step. */
@@ -359,9 +365,10 @@ void edit_group_destroy(edit_group_t h);
 edit_status_t edit_outer_set_profiling(edit_outer_t h, int32_t every);
 
 /* Durations in ms of the last profiled step of `layer`: ms[0] its norm/Gram
- * pass plus its decision kernel, ms[1] its update pass.  With EDIT_ONE_PASS: ms[0] the fused pass, ms[1]
- * the record reduction when the unit was stepped alone (0 in a round, which
- * reduces all units in one launch at its end).  Waits for it. */
+ * pass plus its decision kernel, ms[1] its update pass.  With EDIT_ONE_PASS:
+ * ms[0] the fused pass, ms[1] the record reduction when the unit was stepped
+ * alone (0 in a round, which reduces its units together at its end).  Waits
+ * for it. */
 edit_status_t edit_outer_kernel_times(edit_outer_t h, int32_t layer, float ms[2]);
 
 /* The memory traffic of unit `layer`'s update pass with no arithmetic: a

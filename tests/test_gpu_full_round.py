@@ -4,9 +4,9 @@ The headline 1B-shaped workload (24 units of 51,384,320 elements, K = 8 bf16
 replicas) and six layers of the A-EDiT K = 16 workload (18 units: six
 51,380,224-element matrix units and twelve 2,048-element RMSNorm gains) are
 stepped with edit_outer_step_round in the benchmark's launch configuration
-(the same handle layout, kernel timing on every twelfth unit), so the
-two-unit Gram launches, the single-unit launches that take a pair's
-decisions, the fp64 matrix-core Gram pass and the small launches all run.
+(the same handle layout, kernel timing on every twelfth unit), so batches of
+several units, the timed units' own launches, the fp64 matrix-core Gram pass
+and the small launches of whole units all run.
 
 The EMA state warms up for real from zero (Sec. 3.2): in each warm-up round
 every unit's decision is checked against the oracle's decision on the Gram

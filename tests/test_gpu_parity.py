@@ -179,8 +179,7 @@ def test_llama350m_f32_every_unit_of_a_round():
 def test_llama1b_bf16_full_units_with_anomaly(entry):
     """Llama-1B-shaped units (51,384,320 elements, bf16 replicas, K = 8),
     rounds 18-19: round 19 has one worker x20, which must be masked.  Stepped
-    as one round (unit 0's decision inside unit 11's pass-1 launch) and unit
-    by unit."""
+    as one round (both units in one batch) and unit by unit."""
     wl = synth.get("llama1b-k8-bf16")
     units = [0, 11]
     run = ParityRun(wl, units, DEV, ema_state={u: _expected_ema(wl, u, 18) for u in units})
@@ -214,8 +213,8 @@ def test_llama7b_half_full_unit_clip_active():
 def test_aedit1b_k16_full_layer():
     """A-EDiT round on 1B shapes, K = 16: one layer's matrix unit (51,380,224)
     and its two 2,048-element RMSNorm units, three workers x30.  As one round:
-    the gains are stepped whole in the small launch that takes the matrix
-    unit's decision."""
+    the gains are stepped whole in a launch of their own behind the matrix
+    unit."""
     wl = synth.get("aedit1b-k16-bf16")
     units = [0, 1, 2]
     run = ParityRun(wl, units, DEV, ema_state={u: _expected_ema(wl, u, 10) for u in units})
@@ -289,7 +288,7 @@ def test_resume_from_saved_state_is_bitwise():
 
 @pytest.mark.parametrize("K,dtype", [(8, "bf16"), (4, "f32"), (16, "bf16"), (32, "bf16")])
 def test_round_and_streams_match_unit_by_unit(K, dtype):
-    """A round (each unit's decision folded into the next unit's pass-1 launch)
+    """A round (units in batches, small ones whole in launches of their own)
     and a 3-stream pipeline give the same bits as unit-by-unit calls, over
     several rounds (EMA state carried), units of mixed sizes and a unit order
     that is not the index order."""
@@ -330,11 +329,10 @@ def test_round_and_streams_match_unit_by_unit(K, dtype):
 
 
 # Units whose Gram pass is one block (at most 256 vectors: 2,048 bf16 or
-# 1,024 fp32 elements) ride whole in another unit's pass-1 launch, up to four
-# per launch.  The sizes put six of them first (a launch of riders only, then
-# two riding with the first large unit), one and two between large units,
-# and five at the end (a riders-only launch carrying the last large unit's
-# decision).
+# 1,024 fp32 elements) are stepped whole by a block each, gathered over the
+# round into launches of up to 16 (8 above K = 16).  The sizes put six of them
+# first, one and two between large units, and five at the end; bf16 K = 24 and
+# fp32 K = 32 fill a launch before the round ends.
 _SINGLE_BLOCK_SIZES = {
     "bf16": [0, 1, 7, 8, 2048, 2049, 300_001, 9, 65_537, 255, 2041, 1_000_003, 5, 2047, 16, 3, 2048],
     "f32": [0, 1, 7, 8, 1024, 1027, 300_001, 9, 65_537, 255, 1021, 1_000_003, 5, 1023, 16, 3, 1024],
@@ -377,7 +375,7 @@ def test_single_block_units_in_a_round_match_the_oracle(K, dtype):
 
 @pytest.mark.parametrize("K,dtype", [(2, "bf16"), (8, "bf16"), (8, "f32"), (16, "bf16"), (32, "bf16")])
 def test_single_block_units_in_a_round_match_unit_by_unit(K, dtype):
-    """The same round with single-block units riding in pass-1 launches gives
+    """The same round, its single-block units in launches of their own, gives
     the bits of unit-by-unit edit_outer_step_layer calls, over three rounds
     after the warm-up."""
     sizes = _SINGLE_BLOCK_SIZES[dtype]
@@ -412,23 +410,21 @@ def test_single_block_units_in_a_round_match_unit_by_unit(K, dtype):
         assert x.round == y.round == W + 3
 
 
-# Round schedules around the shared Gram launch (K <= 8; two consecutive
-# units per launch): B = a unit of more than one Gram-pass block, S = a
-# single-block unit.  (name, sizes, timing)
+# Round schedules (K <= 8): B = a unit of more than one Gram-pass block, which
+# shares a batch's launches, S = a single-block unit, which is stepped whole
+# in a launch of such units.  (name, sizes, timing)
 _PAIR_SCHEDULES = [
-    # B B B B B: two pairs, the round's last unit alone
+    # B B B B B: one batch
     ("pairs", [300_001, 65_537, 1_000_003, 40_000, 123_457], 0),
-    # eleven B: five pairs in a row, each launch taking the previous pair's decisions
+    # eleven B: one longer batch
     ("pair_chain", [90_001, 65_537, 40_000, 70_007, 33_333, 100_000, 55_555, 81_920, 47_111, 60_000, 99_999], 0),
-    # B B S B B B S S B: riders after a pair carry both of its decisions
+    # B B S B B B S S B: one batch, the three S after it
     ("pairs_riders", [300_001, 65_537, 2_048, 100_000, 77_777, 50_000, 1_000, 5, 150_001], 0),
-    # B B S: the round ends on a rider that carries a pair's decisions
+    # B B S: a batch and a single S
     ("pair_rider_end", [300_001, 65_537, 33], 0),
-    # nine B with every fourth unit timed: a pair and a unit alone between
-    # timed units
+    # nine B with every fourth unit timed: batches of three between timed units
     ("timed4", [200_003, 65_537, 90_000, 120_001, 40_000, 77_777, 100_000, 50_001, 70_000], 4),
-    # eight B with every third unit timed: a timed unit after a pair takes
-    # both of its decisions
+    # eight B with every third unit timed: batches of two between timed units
     ("timed3", [200_003, 65_537, 90_000, 120_001, 40_000, 77_777, 100_000, 50_001], 3),
 ]
 

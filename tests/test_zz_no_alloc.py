@@ -90,8 +90,8 @@ def test_noalloc_matches_step_layer(K, dtype, sizes):
 
 
 def test_noalloc_refuses_oversized_units_and_one_pass():
-    """K = 32 with 400,003 fp32 elements: 255 Gram-pass blocks of 528
-    partials (1,077,120 bytes) exceed the 1 MiB array; a one-pass handle has
+    """K = 32 with 400,003 fp32 elements: 256 Gram-pass blocks of 528
+    partials (1,081,344 bytes) exceed the 1 MiB array; a one-pass handle has
     no Gram pass to run this way.  Both fail before enqueueing anything."""
     K = 32
     h = EditOuter(OuterConfig(K, [400_003, 1024], "f32"), DEV)
