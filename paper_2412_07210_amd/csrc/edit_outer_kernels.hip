@@ -295,7 +295,7 @@ constexpr int kDecideThreads = 1024;  // one block; wide so the partial loads ov
 // the Infinity Cache or HBM and the reduction is latency-bound: all of a
 // thread's loads for 256 rows are in flight at once up to K = 16, 48 at a
 // time above.  As [NP][rows], whose loads touched a cache line per lane, over
-// up to 1,023 rows the decision kernel took 9.2 us at K = 4 (1.05M fp32 elements; now 4.4), 6.8 at K = 8
+// up to 1,023 rows the decision kernel took 9.2 us at K = 4 (1.05M fp32 elements; now 4.0), 6.8 at K = 8
 // (4.7) and 79 at K = 32 (27, bound by one CU reading 1.1 MB).
 template <int K>
 __device__ void reduce_partials(const double* partials, int rows, double* gram, double* scratch) {
